@@ -221,12 +221,19 @@ def tolerance(case):
 
 
 # ---------------------------------------------------------------- 64 bits
+def _bf16(x):
+    """64-bit values rounded once to bf16's 8 significant bits (a conversion
+    through 32 bits rounds twice)."""
+    m, e = torch.frexp(x)
+    return torch.ldexp(torch.round(m * 256), e - 8)
+
+
 def _step64(case, W, h, y, bias, x_of=None):
     """New states (and, for bf16, their stored values), log-sum-exp and
     logits of one decoder step in 64 bits."""
     W_h, E, W_out = (w.double() for w in W[:3])
     exact_h = torch.tanh(h.double() @ W_h.T + E[y])
-    hs = exact_h.to(torch.bfloat16).double() if case["dtype"] == "bf16" else exact_h
+    hs = _bf16(exact_h) if case["dtype"] == "bf16" else exact_h
     z = (hs if x_of is None else x_of(hs)) @ W_out.T
     z[:, 0] += bias
     return exact_h, hs, torch.logsumexp(z, 1), z
@@ -276,13 +283,13 @@ def _search64(case, seed):
         if hist is not None:
             def x_of(hs):
                 for pl in range(2 * case["kv"]):
-                    hist[rows, p, t - 1, pl] = (hs @ W_kv[pl // 2, pl % 2]).to(torch.bfloat16)
+                    hist[rows, p, t - 1, pl] = _bf16(hs @ W_kv[pl // 2, pl % 2]).to(torch.bfloat16)
                 out = torch.zeros_like(hs)
                 for l in range(case["kv"]):
                     K = hist[rows, p, :t, 2 * l].double()
                     w = torch.softmax((K * hs[:, None, :]).sum(2) / math.sqrt(d), 1)
                     out += (w[:, :, None] * hist[rows, p, :t, 2 * l + 1].double()).sum(1)
-                return (hs + out / case["kv"]).to(torch.bfloat16).double()
+                return _bf16(hs + out / case["kv"])
         _, hs, lse, z = _step64(case, Wd, h[rows, p], last[rows, p], case["beta"] * (t - lx[rows]), x_of)
         v, tk = torch.topk(z, k, dim=1)
         n = len(live)
