@@ -32,7 +32,9 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"f32": 157.3, "bf16": 2516.6}   # dense MFMA, MI355X
+# Dense MFMA, MI355X. The fp32 projection forms each product from three fp16
+# ones (the fp32 MFMA itself peaks at 157.3).
+PEAK_TFLOPS = {"f32": 2516.6 / 3, "bf16": 2516.6}
 HBM_PEAK_BPS = 8.0e12                            # MI355X HBM3E
 
 
@@ -51,7 +53,9 @@ def attainable_proj_seconds(hist, width, d, V, dtype, peak_tflops):
     return t
 # Sources of the projection kernel; measured HBM traffic is reported only
 # while they are unchanged since the counters were taken.
-PROJ_SOURCES = ["paper_2010_02164_amd/csrc/proj.hip", "paper_2010_02164_amd/csrc/topk.h",
+PROJ_SOURCES = ["paper_2010_02164_amd/csrc/proj.hip", "paper_2010_02164_amd/csrc/proj_f32.hip",
+                "paper_2010_02164_amd/csrc/proj_epilogue.h", "paper_2010_02164_amd/csrc/split_f16.h",
+                "paper_2010_02164_amd/csrc/topk.h",
                 "paper_2010_02164_amd/csrc/mfma_common.h", "paper_2010_02164_amd/csrc/wave.h",
                 "paper_2010_02164_amd/csrc/sb_internal.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_proj_traffic.md")

@@ -54,7 +54,8 @@ struct Layout {
   size_t ctrl, q_h0, q_Lx, q_ml, b_input, b_steps, b_sel, b_par, b_ml, b_nout, b_order, s_status, s_score, s_tok, s_h,
       s_row, bp, r_slot, r_hsrc, r_y, r_t, r_Lx, r_lse, hbuf, part, top_lp, top_tok,
       o_count, o_hyp, o_tok, o_pack, o_off, wh_t, kvs, anc, wkv_t, xbuf, attn_part, wout_t, wd3, w_exp, w_ln, w_li,
-      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, total;
+      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, hsplit, total;
+  size_t split;   // bytes of w_scale and hsplit, the last regions
 };
 
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
@@ -152,7 +153,13 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
     L.s_haux = take(nk * sizeof(RowAux));
     L.q_haux = take(Q * sizeof(RowAux));
   }
+  const size_t unsplit = off;
+  if (m.dtype == SB_F32) {
+    L.w_scale = take(S * 128 * 4);
+    L.hsplit = take((Rm + 31) / 32 * 32 * d * 4);
+  }
   L.total = off;
+  L.split = off - unsplit;
   return L;
 }
 
@@ -295,8 +302,15 @@ sb_status launch_timed_step(sb_decoder *dec) {
 
 }  // namespace
 
-// Workspace of the allocation-free decoders (below).
-static __device__ __align__(256) unsigned char scratch[SB_NOALLOC_SCRATCH_BYTES];
+// Workspace of the allocation-free decoders (below). The limit on the shapes
+// they take leaves out the fp32 projection's split states and row scales,
+// which have room of their own behind it: a row's split state is as large as
+// its fp32 state, which the workspace holds twice (candidate and new state),
+// so they are at most half of the limit, plus a 32-row block's padding (of
+// at most 4096 values) and 4 bytes per W_out row of at least 256.
+constexpr size_t SCRATCH_SPLIT_BYTES = SB_NOALLOC_SCRATCH_BYTES / 2 + (4u << 20);
+constexpr size_t SCRATCH_BYTES = SB_NOALLOC_SCRATCH_BYTES + SCRATCH_SPLIT_BYTES;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 namespace {
 
@@ -433,6 +447,10 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
   st.E = model->E;
   st.W_out = model->W_out;
   st.wout_t = w + L.wout_t;
+  if (model->dtype == SB_F32) {
+    st.w_scale = reinterpret_cast<float *>(w + L.w_scale);
+    st.hsplit = w + L.hsplit;
+  }
   st.wh_t = model->dtype == SB_F32 ? reinterpret_cast<const float4 *>(w + L.wh_t) : nullptr;
   st.wh16_t = model->dtype == SB_BF16 ? reinterpret_cast<const uint2 *>(w + L.wh_t) : nullptr;
   const sb_params &p = dec->params;
@@ -538,8 +556,9 @@ sb_status sb_create_noalloc(const sb_model *model, const sb_params *params, void
     set_create_err("sb_create_noalloc: null weight pointer");
     return SB_E_INVALID_ARG;
   }
-  const size_t need = layout_of(*model, *params).total;
-  if (need > SB_NOALLOC_SCRATCH_BYTES) {
+  const Layout L = layout_of(*model, *params);
+  const size_t need = L.total - L.split;
+  if (need > SB_NOALLOC_SCRATCH_BYTES || L.total > SCRATCH_BYTES) {
     char msg[256];
     snprintf(msg, sizeof msg,
              "sb_create_noalloc: these shapes need %zu bytes of workspace; the static scratch holds %zu "
@@ -575,7 +594,7 @@ sb_status sb_create_noalloc(const sb_model *model, const sb_params *params, void
   sb_decoder *dec = new (slot.obj) sb_decoder();
   dec->noalloc = true;
   slot.in_use = true;
-  s = init_decoder(dec, model, params, slot.ptr, SB_NOALLOC_SCRATCH_BYTES, stream);
+  s = init_decoder(dec, model, params, slot.ptr, SCRATCH_BYTES, stream);
   if (s != SB_OK) {
     set_create_err(dec->err.empty() ? "sb_create_noalloc: HIP call failed" : dec->err.c_str());
     (void)hipStreamSynchronize(dec->stream);   // nothing enqueued may still write the scratch

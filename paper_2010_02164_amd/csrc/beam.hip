@@ -18,6 +18,7 @@
 //                backpointer history, one thread per hypothesis.
 #include "mfma_common.h"
 #include "sb_internal.h"
+#include "split_f16.h"
 #include "topk.h"
 #include "wave.h"
 
@@ -75,48 +76,56 @@ __device__ __forceinline__ void wave_lse(float &m, float &s) {
   lse_stage<5>(m, s);
 }
 
-// Logit z[v] of one fp32 row recomputed from W_out and the row's
-// projection input, with the EOS bias of token 0. It follows the
-// projection's arithmetic exactly: each K half in chunks of 32 values, and
-// per chunk, piece q and element e the two fused products of k and k + 16
-// (an fp32 32x32x2 MFMA adds its two products to the sum one after the
-// other, lane half 0's first), then the halves added once, so a recomputed
-// logit equals the projection's bit for bit.
-__device__ __forceinline__ float recompute_logit_f32(const DevState &st, int row, int v) {
-  const int d = st.d;
-  const float *w = static_cast<const float *>(st.W_out) + (size_t)v * d;
-  const float *x = static_cast<const float *>(st.proj_in) + (size_t)row * d;
-  float half[2];
-  for (int g = 0; g < 2; ++g) {
-    float acc = 0.0f;
-    for (int c = g * (d / 2); c < (g + 1) * (d / 2); c += 32)
-      for (int q = 0; q < 4; ++q)
-        for (int e = 0; e < 4; ++e) {
-          const int k0 = c + 4 * q + e;
-          acc = fmaf(w[k0], x[k0], acc);
-          acc = fmaf(w[k0 + 16], x[k0 + 16], acc);
-        }
-    half[g] = acc;
-  }
-  float z = half[0] + half[1];
-  if (v == 0) z += st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
-  return z;
-}
-
-// bf16: the 128 logits of vocabulary tile vt for one row, recomputed by the
+// The 128 logits of vocabulary tile vt for one row, recomputed by the
 // projection's own MFMA sequence so that they equal its logits bit for bit
-// (the bf16 MFMA's internal rounding is not modelled, it is replayed): per
-// 32-row slice, each K half accumulated chunk by chunk and piece by piece
-// from the same W_out fragments and state bytes, then the halves added
-// once. Every column of the MFMA gets the row's state, so all 32 columns
-// hold the same logits; lane (h, l) with l < 16 inserts the logit of
+// (the MFMA's internal rounding is not modelled, it is replayed). Every
+// column of the MFMA gets the row's state, so all 32 columns hold the same
+// logits; per 32-row slice s, lane (h, l) with l < 16 inserts the logit of
 // register l, vocabulary row 32s + 8(l/4) + 4h + l%4 of the tile, into its
 // list (each of the 128 logits once).
+template <int KB>
+__device__ __forceinline__ void insert_slice(const DevState &st, const f16v &z, int v0, int lane, float bias,
+                                             TopK<KB> &tk) {
+  const int h = lane >> 5, l32 = lane & 31;
+  if (l32 >= 16) return;
+  float x = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (r == l32) x = z[r];
+  const int v = v0 + 8 * (l32 >> 2) + 4 * h + (l32 & 3);
+  if (v == 0) x += bias;
+  if (v < st.V) topk_insert(tk, make_key(x, v));
+}
+
+// fp32: the split products chunk by chunk, then the row scales.
+template <int KB>
+__device__ __forceinline__ void recompute_tile_f32(const DevState &st, int row, int vt, int lane, TopK<KB> &tk) {
+  const int nch = st.d / SPLIT_K;
+  const float bias = st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
+  const u4 *x = reinterpret_cast<const u4 *>(st.hsplit + split_state_off(st.d, row, 8 * (lane >> 5)));
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    const u4 *a = reinterpret_cast<const u4 *>(st.wout_t + (size_t)(vt * 4 + s) * nch * SPLIT_CHUNK) + lane;
+    f16v tot = {};
+#pragma unroll 1
+    for (int c = 0; c < nch; ++c) {
+      u4 af[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) af[i] = a[c * (SPLIT_CHUNK / 16) + i * 64];
+      split_chunk(af, x + c * (SPLIT_CHUNK / 16), 64, tot);
+    }
+    const int v0 = vt * 128 + 32 * s;
+    insert_slice(st, SplitScale(st.w_scale + v0 + 4 * (lane >> 5)).apply(tot), v0, lane, bias, tk);
+  }
+}
+
+// bf16: each K half accumulated chunk by chunk and piece by piece, then the
+// halves added once.
 template <int KB>
 __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row, int vt, int lane, TopK<KB> &tk) {
   constexpr int CH = 128, FRAG = 1024;
   const int nk = st.d * 2 / CH, nh = nk >> 1;
-  const int h = lane >> 5, l32 = lane & 31;
+  const int h = lane >> 5;
   const unsigned char *x = static_cast<const unsigned char *>(st.proj_in) + (size_t)row * st.d * 2 + 64 * h;
   const float bias = st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
 #pragma unroll 1
@@ -138,15 +147,10 @@ __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row,
       }
       half[g] = acc;
     }
-    if (l32 < 16) {
-      float z = 0.0f;
+    f16v z;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (r == l32) z = half[0][r] + half[1][r];
-      const int v = vt * 128 + 32 * s + 8 * (l32 >> 2) + 4 * h + (l32 & 3);
-      if (v == 0) z += bias;
-      if (v < st.V) topk_insert(tk, make_key(z, v));
-    }
+    for (int r = 0; r < 16; ++r) z[r] = half[0][r] + half[1][r];
+    insert_slice(st, z, vt * 128 + 32 * s, lane, bias, tk);
   }
 }
 
@@ -291,15 +295,8 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
       const int src = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
       const int vt = t0 + src;
-      if (st.dtype == 1) {
-        recompute_tile_bf16<KB>(st, row, vt, lane, tk);
-      } else {
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int v = vt * 128 + 64 * half + lane;
-          if (v < st.V) topk_insert(tk, make_key(recompute_logit_f32(st, row, v), v));
-        }
-      }
+      if (st.dtype == 1) recompute_tile_bf16<KB>(st, row, vt, lane, tk);
+      else recompute_tile_f32<KB>(st, row, vt, lane, tk);
     }
   }
   mine = 0ull;

@@ -1,5 +1,5 @@
-// Vocabulary projection of the synthetic decoder D (Sec. 2) on gfx950 MFMA,
-// fused with the EOS bias, an online log-sum-exp and a per-row partial top-k:
+// bf16 vocabulary projection of the synthetic decoder D (Sec. 2) on gfx950
+// MFMA (the fp32 one is in proj_f32.hip), fused with the EOS bias, an online log-sum-exp and a per-row partial top-k:
 //   z = W_out h,  z[0] += beta (t - L_x)      [R,d] x [V,d]^T
 // The R x |V| logits never reach memory: each workgroup writes, per row and
 // 128-wide vocabulary tile, (max, sum exp) and its best keys (value, token).
@@ -13,7 +13,7 @@
 //   - 128 vocabulary rows x 5..8 blocks: each wave group takes half of the
 //     blocks and sums the two K halves one after the other into two
 //     accumulator sets, added once at the end;
-//   - bf16 only, 256 vocabulary rows x 4 blocks: K halves as in the first
+//   - 256 vocabulary rows x 4 blocks: K halves as in the first
 //     kind, each wave over 64 vocabulary rows.
 // In all of them an output accumulates its K halves through the same MFMA
 // sequence and adds them once, so a row's result does not depend on the
@@ -30,9 +30,7 @@
 // Blocks of 32 rows past R are neither loaded nor computed.
 #include <algorithm>
 
-#include "mfma_common.h"
-#include "topk.h"
-#include "wave.h"
+#include "proj_epilogue.h"
 
 namespace sb {
 namespace {
@@ -40,10 +38,8 @@ namespace {
 constexpr int THREADS = 512;
 constexpr int NB = 4;            // 32-row batch blocks per workgroup
 constexpr int TR = 32 * NB;      // batch rows per workgroup
-constexpr int TV = GEMM_BV;      // vocabulary rows per workgroup (4 waves x 32)
 constexpr int CH = 128;          // bytes of a row's K chunk
 constexpr int LS = CH + 16;      // padded LDS row stride (bytes)
-constexpr int FRAG = 1024;       // bytes of one wave-wide 16-byte-per-lane fragment
 constexpr int WCH = 4 * FRAG;    // bytes of one wave's W_out fragments per chunk
 
 template <int KB>
@@ -65,7 +61,7 @@ union ProjSmem {
 // With NA = 2 the wave covers two adjacent 32-row vocabulary slices
 // (fragments at abase and abase + WCH) and acc[x * NBV + bb] is slice x,
 // block bb; each state fragment read from LDS then feeds two MFMAs.
-template <bool BF16, int NBV, int D, int NA = 1>
+template <int NBV, int D, int NA = 1>
 __device__ __forceinline__ void proj_mainloop(unsigned char (*Bt)[LS], unsigned char (*Bt1)[LS],
                                               const unsigned char *abase, uint32_t alane,
                                               const unsigned char *bbase, const uint32_t *boff, int srow,
@@ -91,29 +87,22 @@ __device__ __forceinline__ void proj_mainloop(unsigned char (*Bt)[LS], unsigned 
   auto compute = [&](unsigned char (*T)[LS], const u4 *af) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      // K permutation: lane half h at piece q feeds k = chunk + 16h + 4q + e
-      // (fp32) or chunk + 32h + 8q + e (bf16), identically for both operands.
+      // K permutation: lane half h at piece q feeds k = chunk + 32h + 8q + e,
+      // identically for both operands.
       u4 braw[NBV];
 #pragma unroll
       for (int bb = 0; bb < NBV; ++bb) braw[bb] = *reinterpret_cast<const u4 *>(&T[32 * bb + l32][64 * h + 16 * q]);
       // Raised wave priority while this piece's MFMAs issue, so that of the
       // two waves sharing a SIMD the one whose operands are in keeps the
-      // matrix unit fed (fp32 steps of 128-640 rows: 1-2 % faster).
+      // matrix unit fed.
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int bb = 0; bb < NBV; ++bb) {
 #pragma unroll
         for (int x = 0; x < NA; ++x) {
           f16v &c = acc[x * NBV + bb];
-          if constexpr (BF16) {
-            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, af[4 * x + q]),
-                                                        __builtin_bit_cast(bf8, braw[bb]), c, 0, 0, 0);
-          } else {
-            const f4 av = __builtin_bit_cast(f4, af[4 * x + q]);
-            const f4 bv = __builtin_bit_cast(f4, braw[bb]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], c, 0, 0, 0);
-          }
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, af[4 * x + q]),
+                                                      __builtin_bit_cast(bf8, braw[bb]), c, 0, 0, 0);
         }
       }
       __builtin_amdgcn_s_setprio(0);
@@ -154,91 +143,6 @@ __device__ __forceinline__ void proj_mainloop(unsigned char (*Bt)[LS], unsigned 
   }
 }
 
-// Lane-level epilogue of one 32-row block: lane holds batch row l32 of the
-// block and the wave's vocabulary rows v0 + 32wv + 8*(reg/4) + 4h + reg%4
-// (increasing with reg). Adds the EOS bias, folds the 16 logits into
-// (max, sum exp) and a sorted best-KB key list, then combines lanes l and
-// l+32 (same row), which end with identical results. KB = 4 takes a
-// cheaper network than a full sort.
-template <int KB>
-__device__ __forceinline__ void block_lists(const f16v &z, int v0, int wv, int h, int V, float bias, float &m_out,
-                                            float &s_out, TopK<KB> &tk) {
-  float vals[16];
-  if (v0 != 0 && v0 + TV <= V) {   // interior tile: no EOS bias, no rows past V
-#pragma unroll
-    for (int reg = 0; reg < 16; ++reg) vals[reg] = z[reg];
-  } else {
-#pragma unroll
-    for (int reg = 0; reg < 16; ++reg) {
-      const int v = v0 + 32 * wv + 8 * (reg >> 2) + 4 * h + (reg & 3);
-      const float zz = v == 0 ? z[reg] + bias : z[reg];
-      vals[reg] = v < V ? zz : -INFINITY;
-    }
-  }
-  float m = -INFINITY;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) m = fmaxf(m, vals[q]);
-  float s = 0.0f;
-  if (m > -INFINITY) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) s += __expf(vals[q] - m);
-  }
-  // The lane's 16 candidates as ranking keys, sorted by a network.
-  cand_key keys[16];
-#pragma unroll
-  for (int reg = 0; reg < 16; ++reg) keys[reg] = make_key(vals[reg], v0 + 32 * wv + 8 * (reg >> 2) + 4 * h + (reg & 3));
-  TopK<KB> mine;
-  if constexpr (KB == 4) {
-    top4_of_16(keys, mine);
-  } else {
-    bitonic_sort_desc<16>(keys);
-#pragma unroll
-    for (int q = 0; q < KB; ++q) mine.k[q] = keys[q];
-  }
-  TopK<KB> lo, hi;
-#pragma unroll
-  for (int q = 0; q < KB; ++q) stage64<5>(mine.k[q], lo.k[q], hi.k[q]);
-  topk_merge(lo, hi);
-  tk = lo;
-  uint32_t ma, mb, sa, sb;
-  stage32<5>(__float_as_uint(m), ma, mb);
-  stage32<5>(__float_as_uint(s), sa, sb);
-  m = __uint_as_float(ma);
-  s = __uint_as_float(sa);
-  lse_merge(m, s, __uint_as_float(mb), __uint_as_float(sb));
-  m_out = m;
-  s_out = s;
-}
-
-// Partial record of (row j, vocabulary tile vt): the merge of the four
-// vocabulary slices' (max, sum exp, key list), read from LDS.
-template <int KB>
-__device__ __forceinline__ void write_record(const DevState &st, int j, int vt, const float *const *slices) {
-  constexpr int PW = part_width(KB);
-  float m = -INFINITY, s = 0.0f;
-  TopK<KB> tk;
-  topk_init(tk);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const float *p = slices[x];
-    TopK<KB> o;
-    topk_load(o, p + 2);
-    lse_merge(m, s, p[0], p[1]);
-    topk_merge(tk, o);
-  }
-  float rec[PW];
-  rec[0] = m;
-  rec[1] = s;
-  topk_store(rec + 2, tk);
-#pragma unroll
-  for (int x = 2 + 2 * KB; x < PW; ++x) rec[x] = 0.0f;
-  u4 *out = reinterpret_cast<u4 *>(st.part + ((size_t)j * st.S + vt) * PW);
-#pragma unroll
-  for (int x = 0; x < PW / 4; ++x)
-    out[x] = u4{__float_as_uint(rec[4 * x]), __float_as_uint(rec[4 * x + 1]), __float_as_uint(rec[4 * x + 2]),
-                __float_as_uint(rec[4 * x + 3])};
-}
-
 // KV append epilogue of one 32-row block of a wave's 32 outputs (the layout
 // of block_lists): row j's bf16(sum) values go to the KV rows of the
 // expanded candidate, at (beam, level t-1, rank), outputs o0 + 8*(reg/4) +
@@ -272,7 +176,7 @@ struct GemmOperands {
 // Tile of at most 4 blocks (128 rows from r0): the K range is split in two
 // fixed halves, waves 0-3 summing the first, waves 4-7 the second; the two
 // partial sums are added once.
-template <bool BF16, int KB, bool KV>
+template <int KB, bool KV>
 __device__ __forceinline__ void proj_tile_ksplit(const DevState &st, const GemmOperands &op, ProjSmem<KB> &sm, int vt,
                                                  int r0, int R, int nbv) {
   const int d = st.d, V = st.V;
@@ -281,8 +185,8 @@ __device__ __forceinline__ void proj_tile_ksplit(const DevState &st, const GemmO
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = w >> 2, wv = w & 3;               // K half, vocabulary slice
   const int l32 = lane & 31, h = lane >> 5;
-  const int rowbytes = d * (BF16 ? 2 : 4);
-  const int nk = rowbytes / CH;                   // even: d is a multiple of 64 (fp32) / 128 (bf16)
+  const int rowbytes = d * 2;
+  const int nk = rowbytes / CH;                   // even: d is a multiple of 128
   const int nh = nk >> 1;
   const int kbeg = g * nh;
 
@@ -305,10 +209,10 @@ __device__ __forceinline__ void proj_tile_ksplit(const DevState &st, const GemmO
   unsigned char (*Bt1)[LS] = sm.B[1][g];
   const uint32_t alane = (uint32_t)lane * 16u;
   switch (nbv) {
-    case 1: proj_mainloop<BF16, 1, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
-    case 2: proj_mainloop<BF16, 2, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
-    case 3: proj_mainloop<BF16, 3, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
-    default: proj_mainloop<BF16, 4, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
+    case 1: proj_mainloop<1, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
+    case 2: proj_mainloop<2, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
+    case 3: proj_mainloop<3, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
+    default: proj_mainloop<4, 3>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc); break;
   }
 
   // Combine the halves. Half g owns blocks 2g and 2g+1: it sends its sums of
@@ -386,7 +290,7 @@ __device__ __forceinline__ void proj_tile_ksplit(const DevState &st, const GemmO
 // first K half and then over the second, in two accumulators added once at
 // the end: the same order of additions as a K-split tile, so a row's
 // logits do not depend on how the step was tiled.
-template <bool BF16, int KB, bool KV>
+template <int KB, bool KV>
 __device__ __forceinline__ void proj_tile_big(const DevState &st, const GemmOperands &op, ProjSmem<KB> &sm, int vt,
                                               int r0, int R, int nbt) {
   const int d = st.d, V = st.V;
@@ -395,7 +299,7 @@ __device__ __forceinline__ void proj_tile_big(const DevState &st, const GemmOper
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = w >> 2, wv = w & 3;               // row group, vocabulary slice
   const int l32 = lane & 31, h = lane >> 5;
-  const int rowbytes = d * (BF16 ? 2 : 4);
+  const int rowbytes = d * 2;
   const int nk = rowbytes / CH;
   const int nh = nk >> 1;
   const int nbh = (nbt + 1) >> 1;                 // blocks of group 0 (3 or 4)
@@ -428,11 +332,11 @@ __device__ __forceinline__ void proj_tile_big(const DevState &st, const GemmOper
     if (half) __syncthreads();   // the staging tile of the first half is done
     // Both instantiations pass the same barriers (one per chunk).
     if (nbg == 2)
-      proj_mainloop<BF16, 2, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
+      proj_mainloop<2, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
     else if (nbg == 3)
-      proj_mainloop<BF16, 3, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
+      proj_mainloop<3, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
     else
-      proj_mainloop<BF16, 4, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
+      proj_mainloop<4, 2>(Bt, Bt1, abase, alane, bbase, boff, srow, scol, nh, l32, h, acc);
   }
 
   if constexpr (KV) {
@@ -516,7 +420,7 @@ __device__ __forceinline__ void proj_tile_big(const DevState &st, const GemmOper
   }
 }
 
-// Wide tile (bf16, 4-key lists): 256 vocabulary rows x 128 batch rows. Wave
+// Wide tile (4-key lists): 256 vocabulary rows x 128 batch rows. Wave
 // w sums K half w/4 over vocabulary rows 64*(w%4) .. +63 (two 32-row slices)
 // of the 256 and all four blocks, so each state fragment read from LDS
 // feeds two MFMAs (the LDS reads per MFMA halve next to a 32-row wave). The
@@ -548,7 +452,7 @@ __device__ __forceinline__ void proj_tile_wide(const DevState &st, const GemmOpe
   f16v acc[2 * NB];
 #pragma unroll
   for (int b = 0; b < 2 * NB; ++b) acc[b] = f16v{};
-  proj_mainloop<true, NB, 2, 2>(sm.B[0][g], sm.B[1][g], abase, (uint32_t)lane * 16u, bbase, boff, srow, scol, nh,
+  proj_mainloop<NB, 2, 2>(sm.B[0][g], sm.B[1][g], abase, (uint32_t)lane * 16u, bbase, boff, srow, scol, nh,
                                 l32, h, acc);
 
   // Combine the halves, one slice at a time: half g owns blocks 2g, 2g+1,
@@ -615,15 +519,15 @@ __device__ __forceinline__ void proj_tile_wide(const DevState &st, const GemmOpe
 
 // Row tile rt covers blocks bt*rt .. bt*rt + bt - 1 (32 rows each) of
 // vocabulary tile vt.
-template <bool BF16, int KB, bool KV>
+template <int KB, bool KV>
 __device__ __forceinline__ void proj_tile(const DevState &st, const GemmOperands &op, ProjSmem<KB> &sm, int vt, int rt,
                                           int R, int bt) {
   const int r0 = rt * bt * 32;
   const int nbt = min(bt, (R - r0 + 31) >> 5);   // blocks holding valid rows
   if (nbt <= NB)
-    proj_tile_ksplit<BF16, KB, KV>(st, op, sm, vt, r0, R, nbt);
+    proj_tile_ksplit<KB, KV>(st, op, sm, vt, r0, R, nbt);
   else
-    proj_tile_big<BF16, KB, KV>(st, op, sm, vt, r0, R, nbt);
+    proj_tile_big<KB, KV>(st, op, sm, vt, r0, R, nbt);
 }
 
 // Blocks per row tile for a step of R rows: the count (1..8) that minimizes
@@ -657,13 +561,13 @@ __device__ __forceinline__ int row_tile_blocks(int R, int S, int G) {
 // tiles holding rows of this step are visited, and no workgroup is launched
 // just to exit (idle ones would occupy compute units that the dispatcher
 // then withholds from working ones).
-template <bool BF16, int KB, bool KV>
+template <int KB, bool KV>
 __device__ __forceinline__ void tile_walk(const DevState &st, const GemmOperands &op, int nvt) {
   const int R = st.ctrl->R;
   if (R <= 0) return;
-  // bf16 steps whose 256-wide tiles fill at least one round use them.
+  // Steps whose 256-wide tiles fill at least one round use them.
   const int S2 = (nvt + 1) >> 1, nrw = (R + TR - 1) / TR;
-  const bool wide = BF16 && KB == 4 && S2 * nrw >= (int)gridDim.x;
+  const bool wide = KB == 4 && S2 * nrw >= (int)gridDim.x;
   const int bt = wide ? NB : row_tile_blocks(R, nvt, (int)gridDim.x);
   const int nra = wide ? nrw : (R + 32 * bt - 1) / (32 * bt);
   const int T = (wide ? S2 : nvt) * nra;
@@ -675,21 +579,21 @@ __device__ __forceinline__ void tile_walk(const DevState &st, const GemmOperands
     if (idx >= nt) continue;
     const int tile = lo + idx;
     const int vt = tile / nra, rt = tile - vt * nra;
-    if constexpr (BF16 && KB == 4) {
+    if constexpr (KB == 4) {
       if (wide) {
         proj_tile_wide<KB, KV>(st, op, sm, vt, rt * TR, R, nvt);
         __syncthreads();   // LDS is reused by the next tile
         continue;
       }
     }
-    proj_tile<BF16, KB, KV>(st, op, sm, vt, rt, R, bt);
+    proj_tile<KB, KV>(st, op, sm, vt, rt, R, bt);
     __syncthreads();   // LDS is reused by the next tile
   }
 }
 
-template <bool BF16, int KB>
+template <int KB>
 __global__ __launch_bounds__(THREADS, 1) void k_proj(DevState st) {
-  tile_walk<BF16, KB, false>(st, GemmOperands{st.wout_t, st.proj_in}, st.S);
+  tile_walk<KB, false>(st, GemmOperands{st.wout_t, st.proj_in}, st.S);
 }
 
 // KV rows of every expansion of the step: bf16(h . W_kv[l][j]) for the
@@ -698,7 +602,7 @@ __global__ __launch_bounds__(THREADS, 1) void k_proj(DevState st) {
 // not depend on the rows sharing the step), stored at the candidate's
 // (beam, level, rank) place (App. A.2's incremental decoder state).
 __global__ __launch_bounds__(THREADS, 1) void k_kv_append(DevState st) {
-  tile_walk<true, 4, true>(st, GemmOperands{st.wkv_t, st.hbuf}, st.kv_layers * 2 * st.d / TV);
+  tile_walk<4, true>(st, GemmOperands{st.wkv_t, st.hbuf}, st.kv_layers * 2 * st.d / TV);
 }
 
 // W_out [V][d] -> MFMA fragment order [S][nk][4 slices][4 pieces][64 lanes][16 B]:
@@ -750,31 +654,28 @@ __global__ void k_relayout_wkv(const uint16_t *__restrict__ W, unsigned char *__
   }
 }
 
-template <bool BF16>
-hipError_t launch_proj_t(const DevState &st, hipStream_t s) {
-  // Multiple of 8, at most one per compute unit, no more than the 32-row
-  // tiles of a full step (a small vocabulary then still spreads a large step
-  // over the device).
-  const int G = std::max(8, std::min(st.n_cu / 8 * 8, xcd_grid(st.S * ((st.R_max + 31) / 32))));
-  switch (st.tile_keys) {
-    case 4: hipLaunchKernelGGL((k_proj<BF16, 4>), dim3(G), dim3(THREADS), 0, s, st); break;
-    case 8: hipLaunchKernelGGL((k_proj<BF16, 8>), dim3(G), dim3(THREADS), 0, s, st); break;
-    default: hipLaunchKernelGGL((k_proj<BF16, 16>), dim3(G), dim3(THREADS), 0, s, st); break;
-  }
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_relayout_wout(const DevState &st, hipStream_t s) {
-  const int rowbytes = st.d * (st.dtype == 1 ? 2 : 4);
+  if (st.dtype == 0) return launch_split_wout(st, s);
+  const int rowbytes = st.d * 2;
   hipLaunchKernelGGL(k_relayout_wout, dim3(2048), dim3(256), 0, s, static_cast<const unsigned char *>(st.W_out),
                      st.wout_t, st.V, rowbytes, st.S);
   return hipGetLastError();
 }
 
 hipError_t launch_proj(const DevState &st, hipStream_t s) {
-  return st.dtype == 1 ? launch_proj_t<true>(st, s) : launch_proj_t<false>(st, s);
+  if (st.dtype == 0) return launch_proj_split(st, s);
+  // Multiple of 8, at most one per compute unit, no more than the 32-row
+  // tiles of a full step (a small vocabulary then still spreads a large step
+  // over the device).
+  const int G = std::max(8, std::min(st.n_cu / 8 * 8, xcd_grid(st.S * ((st.R_max + 31) / 32))));
+  switch (st.tile_keys) {
+    case 4: hipLaunchKernelGGL((k_proj<4>), dim3(G), dim3(THREADS), 0, s, st); break;
+    case 8: hipLaunchKernelGGL((k_proj<8>), dim3(G), dim3(THREADS), 0, s, st); break;
+    default: hipLaunchKernelGGL((k_proj<16>), dim3(G), dim3(THREADS), 0, s, st); break;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_kv_append(const DevState &st, hipStream_t s) {

@@ -1,0 +1,101 @@
+// Epilogue of the vocabulary projection, shared by its fp32 and bf16
+// kernels: a 32 x 32 block of logits is folded into per-row (max, sum exp)
+// and best keys, and a row's four 32-token slices of a 128-token tile into
+// the tile's partial record.
+#pragma once
+
+#include "mfma_common.h"
+#include "topk.h"
+#include "wave.h"
+
+namespace sb {
+
+constexpr int TV = GEMM_BV;      // vocabulary rows per tile (4 slices x 32)
+constexpr int FRAG = 1024;       // bytes of one wave-wide 16-byte-per-lane fragment
+
+// Lane-level epilogue of one 32-row block: lane holds batch row l32 of the
+// block and the wave's vocabulary rows v0 + 32wv + 8*(reg/4) + 4h + reg%4
+// (increasing with reg). Adds the EOS bias, folds the 16 logits into
+// (max, sum exp) and a sorted best-KB key list, then combines lanes l and
+// l+32 (same row), which end with identical results. KB = 4 takes a
+// cheaper network than a full sort.
+template <int KB>
+__device__ __forceinline__ void block_lists(const f16v &z, int v0, int wv, int h, int V, float bias, float &m_out,
+                                            float &s_out, TopK<KB> &tk) {
+  float vals[16];
+  if (v0 != 0 && v0 + TV <= V) {   // interior tile: no EOS bias, no rows past V
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) vals[reg] = z[reg];
+  } else {
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) {
+      const int v = v0 + 32 * wv + 8 * (reg >> 2) + 4 * h + (reg & 3);
+      const float zz = v == 0 ? z[reg] + bias : z[reg];
+      vals[reg] = v < V ? zz : -INFINITY;
+    }
+  }
+  float m = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) m = fmaxf(m, vals[q]);
+  float s = 0.0f;
+  if (m > -INFINITY) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) s += __expf(vals[q] - m);
+  }
+  // The lane's 16 candidates as ranking keys, sorted by a network.
+  cand_key keys[16];
+#pragma unroll
+  for (int reg = 0; reg < 16; ++reg) keys[reg] = make_key(vals[reg], v0 + 32 * wv + 8 * (reg >> 2) + 4 * h + (reg & 3));
+  TopK<KB> mine;
+  if constexpr (KB == 4) {
+    top4_of_16(keys, mine);
+  } else {
+    bitonic_sort_desc<16>(keys);
+#pragma unroll
+    for (int q = 0; q < KB; ++q) mine.k[q] = keys[q];
+  }
+  TopK<KB> lo, hi;
+#pragma unroll
+  for (int q = 0; q < KB; ++q) stage64<5>(mine.k[q], lo.k[q], hi.k[q]);
+  topk_merge(lo, hi);
+  tk = lo;
+  uint32_t ma, mb, sa, sb;
+  stage32<5>(__float_as_uint(m), ma, mb);
+  stage32<5>(__float_as_uint(s), sa, sb);
+  m = __uint_as_float(ma);
+  s = __uint_as_float(sa);
+  lse_merge(m, s, __uint_as_float(mb), __uint_as_float(sb));
+  m_out = m;
+  s_out = s;
+}
+
+// Partial record of (row j, vocabulary tile vt): the merge of the four
+// vocabulary slices' (max, sum exp, key list), read from LDS.
+template <int KB>
+__device__ __forceinline__ void write_record(const DevState &st, int j, int vt, const float *const *slices) {
+  constexpr int PW = part_width(KB);
+  float m = -INFINITY, s = 0.0f;
+  TopK<KB> tk;
+  topk_init(tk);
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const float *p = slices[x];
+    TopK<KB> o;
+    topk_load(o, p + 2);
+    lse_merge(m, s, p[0], p[1]);
+    topk_merge(tk, o);
+  }
+  float rec[PW];
+  rec[0] = m;
+  rec[1] = s;
+  topk_store(rec + 2, tk);
+#pragma unroll
+  for (int x = 2 + 2 * KB; x < PW; ++x) rec[x] = 0.0f;
+  u4 *out = reinterpret_cast<u4 *>(st.part + ((size_t)j * st.S + vt) * PW);
+#pragma unroll
+  for (int x = 0; x < PW / 4; ++x)
+    out[x] = u4{__float_as_uint(rec[4 * x]), __float_as_uint(rec[4 * x + 1]), __float_as_uint(rec[4 * x + 2]),
+                __float_as_uint(rec[4 * x + 3])};
+}
+
+}  // namespace sb

@@ -9,6 +9,7 @@
 
 #include "bf16_round.h"
 #include "mfma_common.h"
+#include "split_f16.h"
 
 namespace sb {
 namespace {
@@ -122,6 +123,16 @@ __device__ __forceinline__ void rec_tile_f32(const DevState &st, float (*red)[RT
     float *out = static_cast<float *>(st.hbuf) + (size_t)row * d + v0 + i0;
     out[0] = hv[0];
     out[1] = hv[1];
+    // The pair split for the projection (feature v0 + i0 is even: 4 bytes).
+    union {
+      _Float16 f[2];
+      uint32_t u;
+    } hi, lo;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) split_f16(hv[q] * SPLIT_H_SCALE, hi.f[q], lo.f[q]);
+    unsigned char *sp = st.hsplit + split_state_off(d, row, v0 + i0);
+    *reinterpret_cast<uint32_t *>(sp) = hi.u;
+    *reinterpret_cast<uint32_t *>(sp + 1024) = lo.u;
   }
 }
 

@@ -125,10 +125,11 @@ struct DevState {
   const uint2 *wh16_t;
   // model
   const void *W_h, *E, *W_out;
-  // W_out re-laid out tile-contiguous: [S][nk][128 rows][128 bytes], one
-  // 16 KB block per (128-row vocabulary tile, 128-byte K chunk); rows >= V
-  // are zero.
+  // W_out in MFMA fragment order, rows >= V zero: bf16 (k_relayout_wout), or
+  // fp32 split into fp16 pairs (k_split_wout) with the scale of every row.
   unsigned char *wout_t;
+  float *w_scale;          // fp32: [S * 128]
+  unsigned char *hsplit;   // fp32: the step's new states split (split_state_off)
   // sizes and parameters
   int32_t n, k, d, V, M, max_len_cap, refill_thr, S, R_max, dtype, kv_layers, max_inputs;
   int32_t attn;        // 1: projection input = h + layer-mean attention read-out
@@ -179,6 +180,8 @@ hipError_t launch_attn(const DevState &st, hipStream_t s);
 hipError_t launch_backtrack(const DevState &st, int q0, int q1, hipStream_t s);
 hipError_t launch_pack(const DevState &st, int q0, int q1, hipStream_t s);
 hipError_t launch_init(const DevState &st, hipStream_t s);
+hipError_t launch_split_wout(const DevState &st, hipStream_t s);
+hipError_t launch_proj_split(const DevState &st, hipStream_t s);
 hipError_t launch_relayout_wout(const DevState &st, hipStream_t s);
 hipError_t launch_relayout_wkv(const DevState &st, const uint16_t *W_kv, hipStream_t s);
 

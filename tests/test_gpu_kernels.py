@@ -161,3 +161,39 @@ def test_decode_bf16_small_values(gpu, long_row):
     wl = dataclasses.replace(wl, h0=_bf16(h0))
     print(f"[parity] bf16 small values long_row={long_row}", flush=True)
     check_parity(wl, "var_stream")
+
+
+# The fp32 projection splits W_out rows and states into fp16 pairs after a
+# power-of-two scaling per W_out row. Rows of very different magnitude, an
+# outlier inside a row, a zero row and a row of subnormals keep each logit
+# within a few units of 2^-24 of its products' sum of magnitudes.
+@pytest.mark.parametrize("V,d,R,k", [(130, 64, 1, 4), (1000, 192, 33, 12), (8320, 320, 97, 5), (32000, 64, 161, 8)])
+def test_expand_f32_row_scales(gpu, V, d, R, k):
+    rng = np.random.default_rng(41)
+    wl = make_workload(scaled(1, N=4, V=V, d=d, k=k, M=k, n=-(-R // k)))
+    W = wl.W_out.copy()
+    W[1] *= 2.0**12
+    W[2] *= 2.0**-30
+    W[3] = 0.0
+    W[4] = 1e-41
+    W[5, d // 2] = 700.0
+    W[V - 1] *= 2.0**8
+    W[6:64] *= 2.0 ** rng.integers(-8, 6, 58)[:, None]
+    W = W.astype(np.float32)
+    wl = dataclasses.replace(wl, W_out=W)
+    _, _, t, Lx, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, R, 42)
+    print(f"[expand] f32 row scales V={V} d={d} R={R}", flush=True)
+    z = h_ref @ W.astype(np.float64).T
+    z[:, 0] += wl.cfg.beta * (t - Lx)
+    # Per logit: the state's own fp32 error (as in _check_rows, times |w|) and
+    # sqrt(d) roundings of the sum; the log-sum-exp is off by at most the
+    # largest logit's error, plus its own fp32 sum over |V| terms.
+    mag = np.abs(W.astype(np.float64))
+    per_v = (8 * np.sqrt(d) * 2.0**-24 * 4) * np.sqrt((mag**2).sum(1)) + 8 * np.sqrt(d) * 2.0**-24 * (
+        np.abs(h_ref) @ mag.T)
+    tol = per_v.max(1) + 2e-5
+    got = np.take_along_axis(lp_ref, tok, 1)
+    kth = -np.sort(-lp_ref, axis=1)[:, :k]
+    assert np.all(np.abs(lp - got) < tol[:, None])
+    assert np.all(np.abs(-np.sort(-got, axis=1) - kth) < tol[:, None])
+    assert np.all(np.diff(lp, axis=1) <= 1e-12)
