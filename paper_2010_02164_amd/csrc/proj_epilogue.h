@@ -11,6 +11,8 @@
 namespace sb {
 
 constexpr int TV = GEMM_BV;      // vocabulary rows per tile (4 slices x 32)
+constexpr int TILE_BLOCKS = 4;   // 32-row batch blocks per tile, at most
+constexpr int TILE_THREADS = 256;   // 4 waves, each 32 vocabulary rows of the tile
 constexpr int FRAG = 1024;       // bytes of one wave-wide 16-byte-per-lane fragment
 
 // Lane-level epilogue of one 32-row block: lane holds batch row l32 of the
@@ -96,6 +98,37 @@ __device__ __forceinline__ void write_record(const DevState &st, int j, int vt, 
   for (int x = 0; x < PW / 4; ++x)
     out[x] = u4{__float_as_uint(rec[4 * x]), __float_as_uint(rec[4 * x + 1]), __float_as_uint(rec[4 * x + 2]),
                 __float_as_uint(rec[4 * x + 3])};
+}
+
+// Epilogue of a tile of NB blocks (rows from r0) of vocabulary tile vt, by a
+// workgroup of 4 waves: wave wv's lane lists of its 32-token slice of each
+// block (logits z(b)), then one thread per row merges the four slices.
+// Ends with a barrier: LDS may be reused.
+template <int KB, int NB, class Z>
+__device__ __forceinline__ void tile_epilogue(const DevState &st, float (*xch)[32 * TILE_BLOCKS][part_width(KB)],
+                                              Z &&z, int vt, int wv, int r0, int R) {
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int v0 = vt * TV;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int j = r0 + 32 * b + l32;
+    const float bias = (v0 == 0 && j < R) ? st.beta * (float)(st.r_t[j] - st.r_Lx[j]) : 0.0f;
+    float m, s;
+    TopK<KB> tk;
+    block_lists<KB>(z(b), v0, wv, h, st.V, bias, m, s, tk);
+    if (lane < 32) {
+      float *p = xch[wv][32 * b + l32];
+      p[0] = m;
+      p[1] = s;
+      topk_store(p + 2, tk);
+    }
+  }
+  __syncthreads();
+  if (tid < 32 * NB && r0 + tid < R) {
+    const float *sl[4] = {xch[0][tid], xch[1][tid], xch[2][tid], xch[3][tid]};
+    write_record<KB>(st, r0 + tid, vt, sl);
+  }
+  __syncthreads();
 }
 
 }  // namespace sb

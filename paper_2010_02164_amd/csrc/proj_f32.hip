@@ -34,8 +34,8 @@
 namespace sb {
 namespace {
 
-constexpr int THREADS = 256;      // 4 waves, each 32 vocabulary rows of the tile
-constexpr int NBM = 4;            // 32-row batch blocks per tile, at most
+constexpr int THREADS = TILE_THREADS;
+constexpr int NBM = TILE_BLOCKS;
 
 template <int KB>
 union SplitSmem {
@@ -115,37 +115,15 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
   constexpr int D = NB >= 4 ? 2 : NB == 3 ? 3 : 4;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, h = lane >> 5;
   const int nch = st.d / SPLIT_K;
-  const int v0 = vt * TV;
   const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
   f16v tot[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) tot[b] = f16v{};
   split_mainloop<NB, D>(sm.stage, st.wout_t + ((size_t)(vt * 4 + wv) * nch) * SPLIT_CHUNK + lane * 16,
                         st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
-  const SplitScale sc(st.w_scale + v0 + 32 * wv + 4 * h);
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int j = r0 + 32 * b + l32;
-    const float bias = (v0 == 0 && j < R) ? st.beta * (float)(st.r_t[j] - st.r_Lx[j]) : 0.0f;
-    const f16v z = sc.apply(tot[b]);
-    float m, s;
-    TopK<KB> tk;
-    block_lists<KB>(z, v0, wv, h, st.V, bias, m, s, tk);
-    if (lane < 32) {
-      float *p = sm.xch[wv][32 * b + l32];
-      p[0] = m;
-      p[1] = s;
-      topk_store(p + 2, tk);
-    }
-  }
-  __syncthreads();
-  if (tid < 32 * NB && r0 + tid < R) {
-    const float *sl[4] = {sm.xch[0][tid], sm.xch[1][tid], sm.xch[2][tid], sm.xch[3][tid]};
-    write_record<KB>(st, r0 + tid, vt, sl);
-  }
-  __syncthreads();   // LDS is reused by the next tile
+  const SplitScale sc(st.w_scale + vt * TV + 32 * wv + 4 * (lane >> 5));
+  tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return sc.apply(tot[b]); }, vt, wv, r0, R);
 }
 
 // Blocks per row tile for a step of R rows: the count that minimizes the

@@ -197,3 +197,12 @@ def test_expand_f32_row_scales(gpu, V, d, R, k):
     assert np.all(np.abs(lp - got) < tol[:, None])
     assert np.all(np.abs(-np.sort(-got, axis=1) - kth) < tol[:, None])
     assert np.all(np.diff(lp, axis=1) <= 1e-12)
+
+
+@pytest.mark.parametrize("cfg_i,R", [(c, R) for c in (1, 4) for R in (1, 33, 65, 97, 129, 257)])
+def test_expand_tile_heights(gpu, cfg_i, R):
+    """Row tiles of 1 to 4 blocks with a ragged last block, in both types."""
+    wl = make_workload(scaled(cfg_i, N=4, V=8320, d=128, k=5, M=4, n=52))
+    _, _, _, _, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, R, 51)
+    print(f"[expand] {wl.cfg.dtype} R={R}", flush=True)
+    _check_rows(wl, h_gpu, lp, tok, h_ref, lp_ref, lse)
