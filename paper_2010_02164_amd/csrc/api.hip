@@ -28,6 +28,7 @@ struct sb_decoder {
   int32_t *pinned_len = nullptr;   // [2][max_inputs] L_x and max_len staging (none: noalloc)
   int32_t *pinned_flag = nullptr;  // [2] done-flag readback (noalloc: host_flag below)
   int32_t host_flag[2] = {0, 0};   // done-flag readback of a decoder that allocates nothing
+  unsigned char *pinned_dbg = nullptr;   // sb_debug_expand's staging (made by its first call; none: noalloc)
   int device = 0;
   bool noalloc = false;            // lives in the library's static storage (sb_create_noalloc)
   hipEvent_t poll_ev[2] = {nullptr, nullptr};
@@ -238,7 +239,23 @@ __global__ void k_set_queued(DevCtrl *c, int32_t nq) {
   if (c->cursor < nq) c->done = 0;
 }
 
-__global__ void k_set_rows(DevCtrl *c, int32_t R) { c->R = R; }
+// Row metadata of sb_debug_expand: row r reads state r; with `in` ([3][R] in
+// pinned host memory) the tokens, positions and lengths come from there.
+__global__ __launch_bounds__(256) void k_debug_rows(DevState st, const int32_t *in, int32_t R) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r == 0) st.ctrl->R = R;
+  if (r >= R) return;
+  st.r_hsrc[r] = r;
+  if (in) {
+    st.r_y[r] = in[r];
+    st.r_t[r] = in[R + r];
+    st.r_Lx[r] = in[2 * R + r];
+  }
+  if (st.rec_i8) {
+    st.haux[r].F = 1;
+    st.haux[r].n = 0;
+  }
+}
 
 constexpr int BURST = 8;   // timesteps per graph launch / per done-flag poll
 
@@ -850,29 +867,68 @@ sb_status sb_debug_expand(sb_decoder *dec, int32_t R, const void *h_prev, const 
     return SB_E_INVALID_ARG;
   if (st.attn) return SB_E_UNSUPPORTED;
   const size_t es = st.dtype == 1 ? 2 : 4;
-  const size_t rowbytes = (size_t)st.d * es;
-  std::vector<int32_t> src(R);
-  for (int r = 0; r < R; ++r) src[r] = r;   // states placed in slots 0..R-1
-  HIPCHK(hipMemcpyAsync(st.s_h, h_prev, R * rowbytes, hipMemcpyDeviceToDevice, dec->stream));
-  if (st.rec_i8) {
-    HIPCHK(launch_row_digits(st, st.s_h, R, st.s_hd, st.s_haux, dec->stream));
-    HIPCHK(launch_aux_reset(st.haux, R, dec->stream));
+  const size_t rowbytes = (size_t)st.d * es, bytes = R * rowbytes;
+  const size_t N = R, k = st.k;
+  // The call's cost is its small copies, each with a wait of its own (9 of
+  // them took 95 us next to 20 us of kernels), so the row metadata comes and
+  // the results go through one pinned block that the kernels read and write,
+  // and the states are used where the caller has them; one wait at the end.
+  // Unaligned or overlapping state buffers, and decoders that allocate
+  // nothing, take copies as before.
+  if (!dec->pinned_dbg && !dec->noalloc) {
+    const size_t Rm = st.R_max;
+    if (hipHostMalloc(reinterpret_cast<void **>(&dec->pinned_dbg), Rm * (8 + 8 * k + 4 * k + 12), hipHostMallocDefault) !=
+        hipSuccess) {
+      dec->pinned_dbg = nullptr;
+      (void)hipGetLastError();
+    }
   }
-  HIPCHK(hipMemcpyAsync(st.r_hsrc, src.data(), sizeof(int32_t) * R, hipMemcpyHostToDevice, dec->stream));
-  HIPCHK(hipMemcpyAsync(st.r_y, y, sizeof(int32_t) * R, hipMemcpyHostToDevice, dec->stream));
-  HIPCHK(hipMemcpyAsync(st.r_t, t, sizeof(int32_t) * R, hipMemcpyHostToDevice, dec->stream));
-  HIPCHK(hipMemcpyAsync(st.r_Lx, L_x, sizeof(int32_t) * R, hipMemcpyHostToDevice, dec->stream));
-  hipLaunchKernelGGL(k_set_rows, dim3(1), dim3(1), 0, dec->stream, st.ctrl, R);
+  const uintptr_t pi = (uintptr_t)h_prev, po = (uintptr_t)h_out;
+  const bool in_place = ((pi | po) & 15) == 0 && (pi + bytes <= po || po + bytes <= pi);
+  DevState ds = st;
+  int32_t *in = nullptr;
+  if (dec->pinned_dbg) {
+    ds.r_lse = reinterpret_cast<double *>(dec->pinned_dbg);
+    ds.top_lp = ds.r_lse + N;
+    ds.top_tok = reinterpret_cast<int32_t *>(ds.top_lp + N * k);
+    in = ds.top_tok + N * k;
+    memcpy(in, y, 4 * N);
+    memcpy(in + N, t, 4 * N);
+    memcpy(in + 2 * N, L_x, 4 * N);
+  } else {
+    HIPCHK(hipMemcpyAsync(st.r_y, y, 4 * N, hipMemcpyHostToDevice, dec->stream));
+    HIPCHK(hipMemcpyAsync(st.r_t, t, 4 * N, hipMemcpyHostToDevice, dec->stream));
+    HIPCHK(hipMemcpyAsync(st.r_Lx, L_x, 4 * N, hipMemcpyHostToDevice, dec->stream));
+  }
+  hipLaunchKernelGGL(k_debug_rows, dim3((R + 255) / 256), dim3(256), 0, dec->stream, ds, in, R);
   HIPCHK(hipGetLastError());
-  HIPCHK(launch_rec(st, dec->stream));
-  HIPCHK(launch_proj(st, dec->stream));
-  HIPCHK(launch_rowmerge(st, dec->stream));
-  HIPCHK(hipMemcpyAsync(h_out, st.hbuf, R * rowbytes, hipMemcpyDeviceToDevice, dec->stream));
-  HIPCHK(hipMemcpyAsync(lse, st.r_lse, sizeof(double) * R, hipMemcpyDeviceToHost, dec->stream));
-  HIPCHK(hipMemcpyAsync(top_lp, st.top_lp, sizeof(double) * R * st.k, hipMemcpyDeviceToHost, dec->stream));
-  HIPCHK(hipMemcpyAsync(top_tok, st.top_tok, sizeof(int32_t) * R * st.k, hipMemcpyDeviceToHost, dec->stream));
+  if (in_place) {
+    ds.s_h = const_cast<void *>(h_prev);   // read only
+    ds.hbuf = h_out;
+    ds.proj_in = h_out;
+  } else {
+    HIPCHK(hipMemcpyAsync(st.s_h, h_prev, bytes, hipMemcpyDeviceToDevice, dec->stream));
+  }
+  if (st.rec_i8) HIPCHK(launch_row_digits(st, ds.s_h, R, st.s_hd, st.s_haux, dec->stream));
+  HIPCHK(launch_rec(ds, dec->stream));
+  HIPCHK(launch_proj(ds, dec->stream));
+  HIPCHK(launch_rowmerge(ds, dec->stream));
+  if (!in_place) HIPCHK(hipMemcpyAsync(h_out, st.hbuf, bytes, hipMemcpyDeviceToDevice, dec->stream));
+  if (!in) {
+    HIPCHK(hipMemcpyAsync(lse, st.r_lse, 8 * N, hipMemcpyDeviceToHost, dec->stream));
+    HIPCHK(hipMemcpyAsync(top_lp, st.top_lp, 8 * N * k, hipMemcpyDeviceToHost, dec->stream));
+    HIPCHK(hipMemcpyAsync(top_tok, st.top_tok, 4 * N * k, hipMemcpyDeviceToHost, dec->stream));
+  }
+  HIPCHK(launch_init(st, dec->stream));   // the decoder is left reset
   HIPCHK(hipStreamSynchronize(dec->stream));
-  return sb_reset(dec);
+  dec->n_queued = 0;
+  dec->collected = 0;
+  if (in) {
+    memcpy(lse, ds.r_lse, 8 * N);
+    memcpy(top_lp, ds.top_lp, 8 * N * k);
+    memcpy(top_tok, ds.top_tok, 4 * N * k);
+  }
+  return SB_OK;
 }
 
 sb_status sb_debug_slot(sb_decoder *dec, int32_t beam, int32_t rank, int32_t *status, double *score,
@@ -945,6 +1001,7 @@ sb_status sb_destroy(sb_decoder *dec) {
   for (int i = 0; i < 2; ++i)
     if (dec->poll_ev[i]) (void)hipEventDestroy(dec->poll_ev[i]);
   if (dec->pinned_len) (void)hipHostFree(dec->pinned_len);
+  if (dec->pinned_dbg) (void)hipHostFree(dec->pinned_dbg);
   if (dec->pinned_flag && dec->pinned_flag != dec->host_flag) (void)hipHostFree(dec->pinned_flag);
   if (dec->graph_exec) (void)hipGraphExecDestroy(dec->graph_exec);
   if (dec->graph) (void)hipGraphDestroy(dec->graph);

@@ -816,15 +816,6 @@ __global__ __launch_bounds__(256) void k_row_digits(const uint16_t *__restrict__
   }
 }
 
-// Lists of the new states emptied (F = 1: tanh outputs are below 2).
-__global__ void k_aux_reset(RowAux *aux, int count) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < count) {
-    aux[r].F = 1;
-    aux[r].n = 0;
-  }
-}
-
 // W_h, once per decoder: row exponents and empty lists (one wave per row) ...
 __global__ void k_w_exp(DevState st) {
   const int o = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -978,12 +969,6 @@ hipError_t launch_row_digits(const DevState &st, const void *rows, int count, in
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_row_digits, dim3(count), dim3(256), 0, s, static_cast<const uint16_t *>(rows), count, st.d,
                      dig, aux);
-  return hipGetLastError();
-}
-
-hipError_t launch_aux_reset(RowAux *aux, int count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_aux_reset, dim3((count + 255) / 256), dim3(256), 0, s, aux, count);
   return hipGetLastError();
 }
 

@@ -171,7 +171,6 @@ hipError_t launch_rec(const DevState &st, hipStream_t s);
 hipError_t launch_relayout_wh(const DevState &st, hipStream_t s);
 hipError_t launch_rec_prepare(const DevState &st, hipStream_t s);
 hipError_t launch_row_digits(const DevState &st, const void *rows, int count, int8_t *dig, RowAux *aux, hipStream_t s);
-hipError_t launch_aux_reset(RowAux *aux, int count, hipStream_t s);
 hipError_t launch_proj(const DevState &st, hipStream_t s);
 hipError_t launch_rowmerge(const DevState &st, hipStream_t s);
 hipError_t launch_beam(const DevState &st, hipStream_t s);

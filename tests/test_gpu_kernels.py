@@ -206,3 +206,46 @@ def test_expand_tile_heights(gpu, cfg_i, R):
     _, _, _, _, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, R, 51)
     print(f"[expand] {wl.cfg.dtype} R={R}", flush=True)
     _check_rows(wl, h_gpu, lp, tok, h_ref, lp_ref, lse)
+
+
+@pytest.mark.parametrize("cfg_i", [1, 4])
+@pytest.mark.parametrize("form", ["unaligned", "in_place", "noalloc", "again"])
+def test_expand_state_buffers(gpu, cfg_i, form):
+    """The step reads and writes the caller's state buffers where it can
+    (16-byte aligned, not overlapping) and copies otherwise; a decoder that
+    allocates nothing copies its small arrays too. Same bits in every form."""
+    import ctypes
+    import torch
+    from paper_2010_02164_amd import _native as N, decoder_for_workload
+    wl = make_workload(scaled(cfg_i, N=4, V=1000, d=256, k=4, M=4, n=12))
+    R, d, k = 45, 256, 4
+    rng = np.random.default_rng(61)
+    dt = torch.bfloat16 if wl.is_bf16 else torch.float32
+    h = torch.from_numpy(np.tanh(rng.standard_normal((R, d))).astype(np.float32)).cuda().to(dt)
+    y, t, lx = (rng.integers(a, b, R).astype(np.int32) for a, b in ((0, 1000), (1, 40), (3, 40)))
+    dec = decoder_for_workload(wl, max_inputs=4)
+    want = dec.debug_expand(h, y, t, lx)
+    if form == "unaligned":
+        x = torch.empty(R * d + 1, dtype=dt, device="cuda")[1:].view(R, d)
+        x.copy_(h)
+        got = dec.debug_expand(x, y, t, lx)
+    elif form == "in_place":
+        x = h.clone()
+        lse, lp, tok = np.empty(R), np.empty((R, k)), np.empty((R, k), np.int32)
+        I, D = ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double)
+        s = N.lib().sb_debug_expand(dec.handle, R, x.data_ptr(), y.ctypes.data_as(I), t.ctypes.data_as(I),
+                                    lx.ctypes.data_as(I), x.data_ptr(), lse.ctypes.data_as(D), lp.ctypes.data_as(D),
+                                    tok.ctypes.data_as(I))
+        assert s == N.SB_OK
+        got = (x, lse, lp, tok)
+    elif form == "noalloc":
+        nd = decoder_for_workload(wl, max_inputs=4, noalloc=True)
+        got = nd.debug_expand(h, y, t, lx)
+        nd.close()
+    else:   # fewer rows, then the same again through the kept staging
+        dec.debug_expand(h[:7], y[:7], t[:7], lx[:7])
+        got = dec.debug_expand(h, y, t, lx)
+    dec.close()
+    assert torch.equal(got[0], want[0])
+    for g, w in zip(got[1:], want[1:]):
+        assert np.array_equal(g, w)
