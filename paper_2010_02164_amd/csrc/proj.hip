@@ -12,14 +12,15 @@
 // every tile, so a row's result does not depend on the batch or on the
 // tiling.
 //
-// Bound: streaming W_out up to about 64 rows, then the MFMA at the rate the
-// card's power allows (1.1 PFLOP/s in the K loop; a register-only loop of
-// MFMAs on random values clocks down to 1.75) and the epilogue's vector
-// instructions. d = 1024, |V| = 32000, us, against workgroups of 8 waves,
-// one per compute unit, with the K halves on two wave groups (256-wide tiles
-// for large steps): 21 rows 15.9 (17.3), 320 rows 43.9 (53.1), 640 rows 64.6
-// (77.8), 1600 rows 145 (175), 5120 rows 490 (500); at d = 256 265 (315) for
-// 5120 rows, where the epilogue outweighs the K loop.
+// Bound: streaming W_out up to about 64 rows; beyond, latencies inside a
+// wave's K loop (with all loads made trivial it takes 79 % of its time; at
+// 5120 rows the MFMAs are 38 % of a tile's cycles, the epilogue 26 %).
+// d = 1024, |V| = 32000, us, against workgroups of 8 waves, one per compute
+// unit, with the K halves on two wave groups: 21 rows 15.0 (17.3), 389 rows
+// 49.5 (56.0), 640 rows 64.5 (77.8), 1600 rows 148 (175), 5120 rows 450 (500).
+// Storing a chunk's states before the previous chunk's MFMAs instead of
+// after them gave 389 rows 52.0 -> 48.2, 640 rows 67.0 -> 61.4; a third
+// chunk of weights in flight 49.4 and 63.2.
 //
 // The same tile walk, with W_kv in place of W_out and a bf16 store in place
 // of the log-sum-exp / top-k epilogue, appends each expansion's KV rows
@@ -49,33 +50,36 @@ union ProjSmem {
   float xch[4][32 * NBM][part_width(KB)];         // [slice][row][max, sumexp, keys]
 };
 
-// K loop of one wave over one K half of nk chunks: acc[b] += its 32 weight
-// rows x batch block b. Chunk c of the half: weight fragments at abase +
-// c * 16 KB (+ lane * 16 + q * 1 KB), the state tile at bbase + c * 128 bytes
-// (+ boff[u]). Loads of a chunk are issued together, D chunks ahead of use,
-// at indices clamped to the last chunk so that no load sits in a branch.
+// K loop of one wave: acc[half][b] = the sum over a K half of its 32 weight
+// rows x batch block b. Chunk c: weight fragments at abase + c * 16 KB (+
+// lane * 16 + q * 1 KB), the state tile at bbase + c * 128 bytes (+ boff[u]).
+// Weights are loaded D chunks ahead of use into registers; the states one
+// chunk ahead into registers and one into LDS, stored before a chunk's MFMAs
+// so that nothing but the MFMAs stands before the barrier. Loads are at
+// indices clamped to the last chunk, so that none sits in a branch; they
+// complete in issue order, and the scheduling fences keep that order fixed.
 template <int NB, int D>
 __device__ __forceinline__ void proj_mainloop(unsigned char (*stage)[32 * NBM][LS], const unsigned char *abase,
                                               uint32_t alane, const unsigned char *bbase, const uint32_t *boff,
-                                              int nk, f16v *acc) {
+                                              int nk, f16v (*acc)[NB]) {
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int srow = tid >> 3, scol = (tid & 7) * 16;
-  u4 a[D][4], b[D][NB];
+  u4 a[D][4], sg[NB];
   auto loadA = [&](int c, u4 *dst) {
     const unsigned char *p = abase + (uint32_t)c * (uint32_t)(4 * WCH);
 #pragma unroll
     for (int q = 0; q < 4; ++q) dst[q] = *reinterpret_cast<const u4 *>(p + alane + q * FRAG);
   };
-  auto loadB = [&](int c, u4 *dst) {
+  auto loadB = [&](int c) {
     const unsigned char *p = bbase + (uint32_t)c * CH;
 #pragma unroll
-    for (int u = 0; u < NB; ++u) dst[u] = *reinterpret_cast<const u4 *>(p + boff[u]);
+    for (int u = 0; u < NB; ++u) sg[u] = *reinterpret_cast<const u4 *>(p + boff[u]);
   };
-  auto storeB = [&](unsigned char (*T)[LS], const u4 *src) {
+  auto storeB = [&](unsigned char (*T)[LS]) {
 #pragma unroll
-    for (int u = 0; u < NB; ++u) *reinterpret_cast<u4 *>(&T[srow + 32 * u][scol]) = src[u];
+    for (int u = 0; u < NB; ++u) *reinterpret_cast<u4 *>(&T[srow + 32 * u][scol]) = sg[u];
   };
-  auto compute = [&](unsigned char (*T)[LS], const u4 *af) {
+  auto compute = [&](unsigned char (*T)[LS], const u4 *af, f16v *c) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // K permutation: lane half h at piece q feeds k = chunk + 32h + 8q + e,
@@ -85,42 +89,51 @@ __device__ __forceinline__ void proj_mainloop(unsigned char (*stage)[32 * NBM][L
       for (int bb = 0; bb < NB; ++bb) braw[bb] = *reinterpret_cast<const u4 *>(&T[32 * bb + l32][64 * h + 16 * q]);
 #pragma unroll
       for (int bb = 0; bb < NB; ++bb)
-        acc[bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, af[q]),
-                                                          __builtin_bit_cast(bf8, braw[bb]), acc[bb], 0, 0, 0);
+        c[bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, af[q]),
+                                                        __builtin_bit_cast(bf8, braw[bb]), c[bb], 0, 0, 0);
     }
   };
-
-  // Loads complete in issue order, so a wait for one chunk's states also
-  // waits for every load issued before them: the scheduling fences keep the
-  // issue order chunk by chunk (weights, then states), which leaves D-1
-  // chunks in flight at every wait.
-  // Prologue: chunks 0 .. D-1 in flight, chunk 0's states in LDS.
+  loadB(0);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     loadA(min(c, nk - 1), a[c]);
     __builtin_amdgcn_sched_barrier(0);
-    loadB(min(c, nk - 1), b[c]);
-    __builtin_amdgcn_sched_barrier(0);
   }
-  storeB(stage[0], b[0]);
+  storeB(stage[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  loadB(min(1, nk - 1));
   __syncthreads();
-
-  for (int i0 = 0; i0 < nk; i0 += D) {
+  const int nh = nk >> 1;
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int i = i0 + j;   // i % D == j
-      if (i >= nk) break;
-      compute(stage[i & 1], a[j]);
-      __builtin_amdgcn_sched_barrier(0);
-      // States of chunk i+1 sit in b[(j+1) % D]; buffer (i+1)&1 was last
-      // read before the previous barrier.
-      if (i + 1 < nk) storeB(stage[(i + 1) & 1], b[(j + 1) % D]);
-      __builtin_amdgcn_sched_barrier(0);
-      loadA(min(i + D, nk - 1), a[j]);
-      __builtin_amdgcn_sched_barrier(0);
-      loadB(min(i + D, nk - 1), b[j]);
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
+  for (int half = 0; half < 2; ++half) {
+    const int c0 = half * nh, c1 = c0 + nh;
+    if (half)   // chunk c0 + j into a[j]
+      for (int r = nh % D; r > 0; --r) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const u4 t = a[0][q];
+#pragma unroll
+          for (int x = 0; x + 1 < D; ++x) a[x][q] = a[x + 1][q];
+          a[D - 1][q] = t;
+        }
+      }
+    for (int i0 = c0; i0 < c1; i0 += D) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        const int i = i0 + j;
+        if (i >= c1) break;
+        // Chunk i + 1 into the buffer last read before the previous barrier.
+        if (i + 1 < nk) storeB(stage[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        loadB(min(i + 2, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        compute(stage[i & 1], a[j], acc[half]);
+        __builtin_amdgcn_sched_barrier(0);
+        loadA(min(i + D, nk - 1), a[j]);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+      }
     }
   }
 }
@@ -171,25 +184,20 @@ __device__ __forceinline__ void proj_tile(const DevState &st, const GemmOperands
     boff[u] = (uint32_t)min(r0 + (tid >> 3) + 32 * u, R - 1) * (uint32_t)rowbytes + (tid & 7) * 16;
   f16v acc[2][NB];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int b = 0; b < NB; ++b) acc[0][b] = acc[1][b] = f16v{};
+  // Weight fragments of this wave: chunk c at ((vt*nk + c)*4 + wv) * 4 KB.
+  proj_mainloop<NB, D>(sm.B, op.w + ((size_t)vt * nk * 4 + wv) * WCH, (uint32_t)lane * 16u,
+                       static_cast<const unsigned char *>(op.in), boff, nk, acc);
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[half][b] = f16v{};
-    // Weight fragments of this wave: chunk c at ((vt*nk + c)*4 + wv) * 4 KB.
-    proj_mainloop<NB, D>(sm.B, op.w + (((size_t)vt * nk + half * (nk >> 1)) * 4 + wv) * WCH, (uint32_t)lane * 16u,
-                         static_cast<const unsigned char *>(op.in) + half * (nk >> 1) * CH, boff, nk >> 1, acc[half]);
-  }
-  auto z = [&](int b) {
-    f16v x;
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int reg = 0; reg < 16; ++reg) x[reg] = acc[0][b][reg] + acc[1][b][reg];
-    return x;
-  };
+    for (int reg = 0; reg < 16; ++reg) acc[0][b][reg] += acc[1][b][reg];
   if constexpr (KV) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
-      kv_store_block(st, z(b), vt * TV + 32 * wv, lane >> 5, r0 + 32 * b + (lane & 31), R);
+      kv_store_block(st, acc[0][b], vt * TV + 32 * wv, lane >> 5, r0 + 32 * b + (lane & 31), R);
   } else {
-    tile_epilogue<KB, NB>(st, sm.xch, z, vt, wv, r0, R);
+    tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return acc[0][b]; }, vt, wv, r0, R);
   }
 }
 
@@ -234,13 +242,16 @@ __device__ __forceinline__ void tile_walk(const DevState &st, const GemmOperands
   const int bt = row_tile_blocks(R, nvt, st.n_cu);
   const int nra = (R + 32 * bt - 1) / (32 * bt);
   const int T = nvt * nra;
+  const TileOrder order(nvt, nra, 32 * bt * st.d * 2);
   const int x = blockIdx.x & 7, gx = gridDim.x >> 3, j = blockIdx.x >> 3;
   const int lo = (int)((long long)T * x / 8), nt = (int)((long long)T * (x + 1) / 8) - lo;
   for (int r = 0; r * gx < nt; ++r) {
     const int idx = (r & 1) ? (r + 1) * gx - 1 - j : r * gx + j;
     if (idx >= nt) continue;
     const int tile = lo + idx;
-    const int vt = tile / nra, r0 = (tile - vt * nra) * bt * 32;
+    int vt, rt;
+    order.at(tile, vt, rt);
+    const int r0 = rt * bt * 32;
     switch (min(bt, (R - r0 + 31) >> 5)) {
       case 1: proj_tile<KB, KV, 1>(st, op, sm, vt, r0, R); break;
       case 2: proj_tile<KB, KV, 2>(st, op, sm, vt, r0, R); break;

@@ -123,7 +123,9 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
   split_mainloop<NB, D>(sm.stage, st.wout_t + ((size_t)(vt * 4 + wv) * nch) * SPLIT_CHUNK + lane * 16,
                         st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
   const SplitScale sc(st.w_scale + vt * TV + 32 * wv + 4 * (lane >> 5));
-  tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return sc.apply(tot[b]); }, vt, wv, r0, R);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
+  tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R);
 }
 
 // Blocks per row tile for a step of R rows: the count that minimizes the
@@ -163,13 +165,15 @@ __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
   const int bt = split_tile_blocks(R, st.S, st.n_cu);
   const int nra = (R + 32 * bt - 1) / (32 * bt);
   const int T = st.S * nra;
+  const TileOrder order(st.S, nra, 32 * bt * st.d * 4);
   const int x = blockIdx.x & 7, gx = gridDim.x >> 3, j = blockIdx.x >> 3;
   const int lo = (int)((long long)T * x / 8), nt = (int)((long long)T * (x + 1) / 8) - lo;
   for (int r = 0; r * gx < nt; ++r) {
     const int idx = (r & 1) ? (r + 1) * gx - 1 - j : r * gx + j;
     if (idx >= nt) continue;
     const int tile = lo + idx;
-    const int vt = tile / nra, rt = tile - vt * nra;
+    int vt, rt;
+    order.at(tile, vt, rt);
     const int r0 = rt * bt * 32;
     switch (min(bt, (R - r0 + 31) >> 5)) {
       case 1: split_tile<KB, 1>(st, sm, vt, r0, R); break;
