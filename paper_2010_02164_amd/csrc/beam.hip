@@ -25,24 +25,29 @@
 namespace sb {
 namespace {
 
-// Wave-wide maximum of a 64-bit key, in every lane.
+// Maximum of a 64-bit key, in every lane.
 template <int S>
 __device__ __forceinline__ cand_key max_stage(cand_key x) {
   cand_key a, b;
   stage64<S>(x, a, b);
   return a > b ? a : b;
 }
-__device__ __forceinline__ cand_key wave_max_key(cand_key x) {
+// Over the G lanes of a row (8 or 64).
+template <int G>
+__device__ __forceinline__ cand_key group_max_key(cand_key x) {
   x = max_stage<0>(x);
   x = max_stage<1>(x);
   x = max_stage<2>(x);
-  x = max_stage<3>(x);
-  x = max_stage<4>(x);
-  return max_stage<5>(x);
+  if constexpr (G == 64) {
+    x = max_stage<3>(x);
+    x = max_stage<4>(x);
+    x = max_stage<5>(x);
+  }
+  return x;
 }
 
-// Wave-wide log-sum-exp combine of (max, sum exp) pairs; every lane ends
-// with the same result. The merge is not symmetric in its operands once
+// Log-sum-exp combine of (max, sum exp) pairs over the G lanes of a row;
+// every lane ends with the same result. The merge is not symmetric in its operands once
 // the compiler fuses a product into the sum, so both lanes of a pair take
 // them in the same order: the lower lane's first (the swap stages 4 and 5
 // already hand both lanes the pair in that order).
@@ -67,13 +72,16 @@ __device__ __forceinline__ void lse_stage(float &m, float &s) {
   m = M;
   s = Sm;
 }
-__device__ __forceinline__ void wave_lse(float &m, float &s) {
+template <int G>
+__device__ __forceinline__ void group_lse(float &m, float &s) {
   lse_stage<0>(m, s);
   lse_stage<1>(m, s);
   lse_stage<2>(m, s);
-  lse_stage<3>(m, s);
-  lse_stage<4>(m, s);
-  lse_stage<5>(m, s);
+  if constexpr (G == 64) {
+    lse_stage<3>(m, s);
+    lse_stage<4>(m, s);
+    lse_stage<5>(m, s);
+  }
 }
 
 // The 128 logits of vocabulary tile vt for one row, recomputed by the
@@ -154,11 +162,12 @@ __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row,
   }
 }
 
-// Merge the per-tile partials of one row (one wave). Each lane folds the
-// tiles lane, lane+64, ... into (max, sum exp) and a sorted best-KB list
+// Merge the per-tile partials of one row by G lanes (a wave, or 8 lanes when
+// there are at most 8 tiles; `lane` counts within them). Each lane folds the
+// tiles lane, lane+G, ... into (max, sum exp) and a sorted best-KB list
 // (loads issued a batch at a time before they are folded). The row's
 // log-sum-exp is combined over the lanes and taken from lane 0; the row's k
-// best keys are drawn in k rounds of a wave maximum over the lists' heads,
+// best keys are drawn in k rounds of a maximum over the lists' heads,
 // the lane holding the winner dropping it (keys are distinct: they carry
 // the token). Lane r < k receives the key of rank r.
 //
@@ -169,23 +178,24 @@ __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row,
 // lists in place of the record's keys, and the k keys are drawn again. Any
 // other tile's unkept keys rank below its last kept key, so at most at the
 // k-th key drawn, and adding candidates can only raise the k-th key.
-template <int KB, int TK>
+// (With full lists, TK = KB >= k, no tile can hold more of the best k.)
+template <int KB, int TK, int G>
 __device__ __forceinline__ double merge_row(const DevState &st, int row, int lane, int k, cand_key &mine) {
   constexpr int PW = part_width(TK);
   // Partials in flight per lane (full-length lists come with fewer than 64
   // tiles, one per lane).
-  constexpr int NBT = TK == TILE_KEYS_SHORT ? 4 : 1;
+  constexpr int NBT = TK == TILE_KEYS_SHORT && G == 64 ? 4 : 1;
   const float *base = st.part + (size_t)row * st.S * PW;
   float m = -INFINITY, s = 0.0f;
   TopK<KB> tk;
   topk_init(tk);
   cand_key last_max = 0ull;   // largest last kept key over the lane's tiles
 #pragma unroll 1
-  for (int t0 = lane; t0 < st.S; t0 += 64 * NBT) {
+  for (int t0 = lane; t0 < st.S; t0 += G * NBT) {
     float rec[NBT][PW];
 #pragma unroll
     for (int u = 0; u < NBT; ++u) {
-      const int t = min(t0 + 64 * u, st.S - 1);
+      const int t = min(t0 + G * u, st.S - 1);
       const uint4 *p = reinterpret_cast<const uint4 *>(base + (size_t)t * PW);
 #pragma unroll
       for (int x = 0; x < PW / 4; ++x) {
@@ -202,7 +212,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
       TopK<4> run[4];
 #pragma unroll
       for (int u = 0; u < NBT; ++u) {
-        const bool ok = t0 + 64 * u < st.S;
+        const bool ok = t0 + G * u < st.S;
         topk_load(run[u], rec[u] + 2);
 #pragma unroll
         for (int j = 0; j < 4; ++j) run[u].k[j] = ok ? run[u].k[j] : 0ull;
@@ -237,7 +247,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
     } else {
 #pragma unroll
       for (int u = 0; u < NBT; ++u) {
-        if (t0 + 64 * u < st.S) {
+        if (t0 + G * u < st.S) {
           TopK<TK> t4;
           topk_load(t4, rec[u] + 2);
           TopK<KB> o;
@@ -251,12 +261,12 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
       }
     }
   }
-  wave_lse(m, s);
+  group_lse<G>(m, s);
   cand_key kth = 0ull;
   mine = 0ull;
 #pragma unroll 1
   for (int r = 0; r < k; ++r) {
-    const cand_key best = wave_max_key(tk.k[0]);
+    const cand_key best = group_max_key<G>(tk.k[0]);
     if (lane == r) mine = best;
     kth = best;
     if (tk.k[0] == best) {
@@ -266,8 +276,8 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
     }
   }
   // The row's log-sum-exp as lane 0 has it, for every lane.
-  const double lse = __shfl((double)m + log((double)s), 0, 64);
-  if (__ballot(last_max > kth) == 0ull) return lse;
+  const double lse = __shfl((double)m + log((double)s), 0, G);
+  if (G < 64 || __ballot(last_max > kth) == 0ull) return lse;
 
   // Rare path: rebuild the lists with the saturated tiles recomputed.
   topk_init(tk);
@@ -302,7 +312,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
   mine = 0ull;
 #pragma unroll 1
   for (int r = 0; r < k; ++r) {
-    const cand_key best = wave_max_key(tk.k[0]);
+    const cand_key best = group_max_key<G>(tk.k[0]);
     if (lane == r) mine = best;
     if (tk.k[0] == best) {
 #pragma unroll
@@ -323,7 +333,7 @@ __global__ __launch_bounds__(256) void k_rowmerge(DevState st) {
   if (row >= R) return;
   cand_key mine;
   const int k = st.k;
-  const double lse = merge_row<KB, TK>(st, row, lane, k, mine);
+  const double lse = merge_row<KB, TK, 64>(st, row, lane, k, mine);
   if (lane == 0) st.r_lse[row] = lse;
   if (lane < k) {
     st.top_lp[(size_t)row * k + lane] = (double)key_val(mine) - lse;
@@ -337,12 +347,17 @@ __device__ __forceinline__ bool ranks_above(double sa, int ka, double sb, int kb
   return sa > sb || (sa == sb && ka < kb);
 }
 
-// Threads of a beam workgroup: 8 waves (a wave per parent row), or 4 waves
-// when the vocabulary has at most 8 tiles and a row's merge is short (four
-// workgroups then share a compute unit). Both hold a thread per candidate
-// of the ranking up to k = 15.
+// Threads of a beam workgroup, at least one per candidate of the ranking (k *
+// (k + 1) of them):
+//  - up to 8 vocabulary tiles and k <= 7: one wave, 8 lanes per parent row, so
+//    that a beam takes one wave slot and its steps no barrier (|V| = 256, 2048
+//    records, k = 5: 24.0 us with 4 waves, 10.9 with one; |V| = 1000, 8 records, k = 4: 8.7 and
+//    6.8);
+//  - up to 8 tiles, k <= 15: 4 waves, a wave per parent row;
+//  - else 8 waves, a wave per parent row.
 constexpr int BEAM_THREADS = 512;
 constexpr int BEAM_THREADS_SMALL = 256;
+constexpr int BEAM_THREADS_WAVE = 64;
 constexpr int NO_KEY = 0x7FFFFFFF;
 
 // A candidate expansion of the per-beam ranking (16 bytes, one LDS read).
@@ -353,7 +368,8 @@ struct Cand {
 
 template <int KB, int TK, int NT>
 __global__ __launch_bounds__(NT) void k_beam(DevState st) {
-  constexpr int BEAM_WAVES = NT / 64;
+  constexpr int G = NT == BEAM_THREADS_WAVE ? 8 : 64;                       // lanes per parent row
+  constexpr int T1 = NT > 64 ? 64 : 0, T2 = NT > 128 ? 128 : 0;             // threads with work of their own
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -371,7 +387,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     my_score = st.s_score[base + tid];
   }
   int my_q = 0, my_t = 0, my_ml = 0, my_nout = 0;
-  if (tid == 64) {
+  if (tid == T1) {
     my_q = st.b_input[b];
     my_t = st.b_steps[b] + 1;     // 1-based index of the emitted token
     my_ml = st.b_ml[b];
@@ -402,7 +418,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     sl_row[tid] = my_row;
     sl_score[tid] = my_score;
   }
-  if (tid == 64) {
+  if (tid == T1) {
     q_in_sh = my_q;
     t_sh = my_t;
     max_len_sh = my_ml;
@@ -411,14 +427,16 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   __syncthreads();
   const int q_in = q_in_sh, t = t_sh, max_len = max_len_sh, nout0 = nout_sh;
 
-  // Row merge of every active parent: wave w takes parents w, w+8.
-  for (int par = wave; par < k; par += BEAM_WAVES) {
+  // Row merge of every active parent: wave w takes parents w, w + NT / 64, ...,
+  // or all of them 8 lanes each.
+  for (int par = tid / G; par < k; par += NT / G) {
     if (sl_status[par] != SLOT_ACTIVE) continue;
+    const int gl = lane % G;
     cand_key mine;
-    const double lse = merge_row<KB, TK>(st, sl_row[par], lane, KC, mine);
-    if (lane < KC) {
-      ch_lp[par * KC + lane] = (double)key_val(mine) - lse;
-      ch_tok[par * KC + lane] = key_idx(mine);
+    const double lse = merge_row<KB, TK, G>(st, sl_row[par], gl, KC, mine);
+    if (gl < KC) {
+      ch_lp[par * KC + gl] = (double)key_val(mine) - lse;
+      ch_tok[par * KC + gl] = key_idx(mine);
     }
   }
   __syncthreads();
@@ -567,8 +585,8 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     const uint32_t tokbits = ntok[tid] < 0 ? BP_NOOP : (uint32_t)ntok[tid];
     bprow[tid] = ((uint32_t)npar[tid] << 24) | tokbits;
   }
-  if (fairseq && tid >= 64 && tid < 64 + no) {
-    const int f = tid - 64;
+  if (fairseq && tid >= T1 && tid < T1 + no) {
+    const int f = tid - T1;
     bprow[k + f] = ((uint32_t)opar[f] << 24) | (uint32_t)otok[f];
     OutHyp h;
     h.score = oscore[f];
@@ -601,7 +619,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
       // Y[i] = the outputs in the order they were finalized; those of
       // earlier steps get the finishing timestep too.
       total = nout0 + no;
-      if (tid >= 128 && tid < 128 + nout0) st.o_hyp[(size_t)q_in * k + (tid - 128)].finalize_step = fin;
+      if (tid >= T2 && tid < T2 + nout0) st.o_hyp[(size_t)q_in * k + (tid - T2)].finalize_step = fin;
     }
     if (tid < k) {
       st.s_status[base + tid] = SLOT_EMPTY;
@@ -744,11 +762,18 @@ hipError_t launch_rowmerge(const DevState &st, hipStream_t s) {
 
 hipError_t launch_beam(const DevState &st, hipStream_t s) {
   const bool sh = st.tile_keys == TILE_KEYS_SHORT;
-  const bool small = st.S <= 8 && st.k <= 15;   // short row merges: 4-wave workgroups
-#define SB_BEAM(KB, TK)                                                                               \
-  do {                                                                                                \
-    if (small) hipLaunchKernelGGL((k_beam<KB, TK, BEAM_THREADS_SMALL>), dim3(st.n), dim3(BEAM_THREADS_SMALL), 0, s, st); \
-    else hipLaunchKernelGGL((k_beam<KB, TK, BEAM_THREADS>), dim3(st.n), dim3(BEAM_THREADS), 0, s, st); \
+  const bool small = st.S <= 8 && st.k <= 15, wave = st.S <= 8 && st.k <= 7;
+#define SB_BEAM_NT(KB, TK, NT) hipLaunchKernelGGL((k_beam<KB, TK, NT>), dim3(st.n), dim3(NT), 0, s, st)
+#define SB_BEAM(KB, TK)                                                            \
+  do {                                                                             \
+    if constexpr (KB <= 8 && TK == KB) {                                           \
+      if (wave) {                                                                  \
+        SB_BEAM_NT(KB, TK, BEAM_THREADS_WAVE);                                     \
+        break;                                                                     \
+      }                                                                            \
+    }                                                                              \
+    if (small) SB_BEAM_NT(KB, TK, BEAM_THREADS_SMALL);                             \
+    else SB_BEAM_NT(KB, TK, BEAM_THREADS);                                         \
   } while (0)
   switch (st.kbucket) {
     case 4: SB_BEAM(4, 4); break;
@@ -762,6 +787,7 @@ hipError_t launch_beam(const DevState &st, hipStream_t s) {
       break;
   }
 #undef SB_BEAM
+#undef SB_BEAM_NT
   return hipGetLastError();
 }
 

@@ -197,3 +197,13 @@ def test_collect_in_pieces_through_the_c_abi(gpu):
     dec.close()
     assert truncated > 0 and calls > 2
     assert got == [(h.input, h.rank, h.tokens, h.score, h.status) for h in ref]
+
+
+@pytest.mark.parametrize("V,k,sched", [(256, 7, "var_stream"), (1024, 7, "fixed_fairseq"), (1024, 1, "var_cap"),
+                                       (1025, 7, "var_fifo"), (1000, 8, "var_stream"), (130, 5, "fixed_fairseq_stream")])
+def test_small_vocabulary_beams(gpu, V, k, sched):
+    """Beams of at most 8 vocabulary tiles, merged 8 lanes per row up to k = 7,
+    and their neighbours on either side of the limits."""
+    wl = make_workload(scaled(1, N=40, n=6, V=V, k=k, M=max(1, k - 1)))
+    print(f"[parity] small vocabulary V={V} k={k} {sched}", flush=True)
+    check_parity(wl, sched, pool=12 if sched == "var_cap" else None)
