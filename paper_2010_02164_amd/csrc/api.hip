@@ -52,11 +52,11 @@ namespace {
 constexpr size_t ALIGN = 256;
 
 struct Layout {
-  size_t ctrl, q_h0, q_Lx, q_ml, b_input, b_steps, b_sel, b_par, b_ml, b_nout, b_order, s_status, s_score, s_tok, s_h,
-      s_row, bp, r_slot, r_hsrc, r_y, r_t, r_Lx, r_lse, hbuf, part, top_lp, top_tok,
+  size_t ctrl, q_h0, q_Lx, q_ml, b_input, b_steps, b_row0, b_mask, b_Lx, b_par, b_ml, b_nout, b_order, s_status, s_score, s_tok, s_h,
+      bp, r_slot, r_hsrc, r_y, r_t, r_Lx, r_lse, hbuf, part, top_lp, top_tok,
       o_count, o_hyp, o_tok, o_pack, o_off, wh_t, kvs, anc, wkv_t, xbuf, attn_part, wout_t, wd3, w_exp, w_ln, w_li,
       w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, hsplit, total;
-  size_t split;   // bytes of w_scale and hsplit, the last regions
+  size_t extra;   // bytes of the last regions: w_scale, hsplit, b_Lx
 };
 
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
@@ -100,7 +100,8 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
   L.q_ml = take(Q * 4);
   L.b_input = take(n * 4);
   L.b_steps = take(n * 4);
-  L.b_sel = take(n * 4);
+  L.b_row0 = take(n * 4);
+  L.b_mask = take(n * 4);
   L.b_par = take(n * 4);
   L.b_ml = take(n * 4);
   L.b_nout = take(n * 4);
@@ -109,7 +110,6 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
   L.s_score = take(nk * 8);
   L.s_tok = take(nk * 4);
   L.s_h = take(nk * d * es);
-  L.s_row = take(nk * 4);
   L.bp = take(Q * MLC * bpw * 4);
   L.r_slot = take(Rm * 4);
   L.r_hsrc = take(Rm * 4);
@@ -154,13 +154,14 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
     L.s_haux = take(nk * sizeof(RowAux));
     L.q_haux = take(Q * sizeof(RowAux));
   }
-  const size_t unsplit = off;
+  const size_t before = off;
+  L.b_Lx = take(n * 4);
   if (m.dtype == SB_F32) {
     L.w_scale = take(S * 128 * 4);
     L.hsplit = take((Rm + 31) / 32 * 32 * d * 4);
   }
   L.total = off;
-  L.split = off - unsplit;
+  L.extra = off - before;
   return L;
 }
 
@@ -320,13 +321,13 @@ sb_status launch_timed_step(sb_decoder *dec) {
 }  // namespace
 
 // Workspace of the allocation-free decoders (below). The limit on the shapes
-// they take leaves out the fp32 projection's split states and row scales,
-// which have room of their own behind it: a row's split state is as large as
-// its fp32 state, which the workspace holds twice (candidate and new state),
-// so they are at most half of the limit, plus a 32-row block's padding (of
-// at most 4096 values) and 4 bytes per W_out row of at least 256.
-constexpr size_t SCRATCH_SPLIT_BYTES = SB_NOALLOC_SCRATCH_BYTES / 2 + (4u << 20);
-constexpr size_t SCRATCH_BYTES = SB_NOALLOC_SCRATCH_BYTES + SCRATCH_SPLIT_BYTES;
+// they take leaves out the last regions (Layout::extra), which have room of
+// their own behind it: a row's split state is as large as its fp32 state,
+// which the workspace holds twice (candidate and new state), so the split
+// states are at most half of the limit, plus a 32-row block's padding (of at
+// most 4096 values), 4 bytes per W_out row of at least 256 and 4 per beam.
+constexpr size_t SCRATCH_EXTRA_BYTES = SB_NOALLOC_SCRATCH_BYTES / 2 + (4u << 20);
+constexpr size_t SCRATCH_BYTES = SB_NOALLOC_SCRATCH_BYTES + SCRATCH_EXTRA_BYTES;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 namespace {
@@ -407,7 +408,9 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
   st.q_ml = reinterpret_cast<int32_t *>(w + L.q_ml);
   st.b_input = reinterpret_cast<int32_t *>(w + L.b_input);
   st.b_steps = reinterpret_cast<int32_t *>(w + L.b_steps);
-  st.b_sel = reinterpret_cast<int32_t *>(w + L.b_sel);
+  st.b_row0 = reinterpret_cast<int32_t *>(w + L.b_row0);
+  st.b_mask = reinterpret_cast<uint32_t *>(w + L.b_mask);
+  st.b_Lx = reinterpret_cast<int32_t *>(w + L.b_Lx);
   st.b_par = reinterpret_cast<int32_t *>(w + L.b_par);
   st.b_ml = reinterpret_cast<int32_t *>(w + L.b_ml);
   st.b_nout = reinterpret_cast<int32_t *>(w + L.b_nout);
@@ -416,7 +419,6 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
   st.s_score = reinterpret_cast<double *>(w + L.s_score);
   st.s_tok = reinterpret_cast<int32_t *>(w + L.s_tok);
   st.s_h = w + L.s_h;
-  st.s_row = reinterpret_cast<int32_t *>(w + L.s_row);
   st.bp = reinterpret_cast<uint32_t *>(w + L.bp);
   st.r_slot = reinterpret_cast<int32_t *>(w + L.r_slot);
   st.r_hsrc = reinterpret_cast<int32_t *>(w + L.r_hsrc);
@@ -574,7 +576,7 @@ sb_status sb_create_noalloc(const sb_model *model, const sb_params *params, void
     return SB_E_INVALID_ARG;
   }
   const Layout L = layout_of(*model, *params);
-  const size_t need = L.total - L.split;
+  const size_t need = L.total - L.extra;
   if (need > SB_NOALLOC_SCRATCH_BYTES || L.total > SCRATCH_BYTES) {
     char msg[256];
     snprintf(msg, sizeof msg,

@@ -379,11 +379,12 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   const int KC = k + (fairseq ? 1 : 0);   // children drawn per parent
   // Everything the beam needs from its records is loaded in one round,
   // before the selection flag is tested.
-  int my_status = SLOT_EMPTY, my_row = -1;
+  const int row0 = st.b_row0[b];
+  const uint32_t active = st.b_mask[b] & 0xFFFFu;
+  int my_status = SLOT_EMPTY;
   double my_score = 0.0;
   if (tid < k) {
     my_status = st.s_status[base + tid];
-    my_row = st.s_row[base + tid];
     my_score = st.s_score[base + tid];
   }
   int my_q = 0, my_t = 0, my_ml = 0, my_nout = 0;
@@ -396,8 +397,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   // The KV ancestry buffer holding this beam's current ranks (read before
   // thread 0 flips the parity at the end of the step).
   const int apar = st.kv_layers > 0 ? st.b_par[b] : 0;
-  // b_sel is cleared for every beam when nothing is live (R == 0).
-  if (!st.b_sel[b]) return;
+  if (row0 < 0) return;   // not expanded (every beam when nothing is live)
   __shared__ int sl_status[KMAX_SUPPORTED], sl_row[KMAX_SUPPORTED];
   __shared__ double sl_score[KMAX_SUPPORTED];
   __shared__ int q_in_sh, t_sh, max_len_sh, nout_sh;
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   __shared__ int r_key[2 * KMAX_SUPPORTED];
   if (tid < k) {
     sl_status[tid] = my_status;
-    sl_row[tid] = my_row;
+    sl_row[tid] = row0 + __popc(active & ((1u << tid) - 1u));   // of an active candidate
     sl_score[tid] = my_score;
   }
   if (tid == T1) {
@@ -643,6 +643,11 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     } else {
       st.s_status[base + tid] = SLOT_EMPTY;
     }
+  }
+  if (wave == 0) {
+    const int status = lane < w ? nstat[lane] : SLOT_EMPTY;
+    const unsigned long long am = __ballot(status == SLOT_ACTIVE), tm = __ballot(status > SLOT_ACTIVE);
+    if (lane == 0) st.b_mask[b] = (uint32_t)am | (uint32_t)tm << 16;
   }
   if (tid == 0) {
     st.b_steps[b] = t;

@@ -61,7 +61,9 @@ struct DevState {
   // beams [n] (n = the pool of cached beams)
   int32_t *b_input;    // queue position, -1 = free
   int32_t *b_steps;    // l_t: steps taken
-  int32_t *b_sel;      // 1 if expanded this step
+  int32_t *b_row0;     // first row of the beam this step (its active candidates in rank order), -1: not expanded
+  uint32_t *b_mask;    // candidates by rank: active (bits 0..15), terminated (bits 16..31)
+  int32_t *b_Lx;       // L_x of the beam's input
   int32_t *b_par;      // which KV buffer holds this beam's state
   int32_t *b_ml;       // max_len of the beam's input
   int32_t *b_nout;     // outputs already finalized (Fairseq rule)
@@ -71,7 +73,6 @@ struct DevState {
   double *s_score;
   int32_t *s_tok;      // last token (0 for a fresh beam: the start symbol)
   void *s_h;           // [n*k][d] state after consuming the candidate's tokens
-  int32_t *s_row;      // row of the slot this step, -1 if not expanded
   uint32_t *bp;        // [max_inputs][max_len_cap][bpw] backpointers, by queue position
   // rows [R_max]: per-row metadata written by the scheduler
   int32_t *r_slot;     // slot of the expanded candidate

@@ -15,7 +15,10 @@ namespace {
 
 constexpr int SCHED_THREADS = 1024;   // at most; a launch takes one wave per 64 x PER beams
 
-// Exclusive prefix sum across the workgroup; *total receives the sum.
+constexpr int NWMAX = SCHED_THREADS / 64;
+
+// Exclusive prefix sum across the workgroup; *total receives the sum. `sm`:
+// one word per wave, not used by another scan until a barrier has passed.
 __device__ int block_excl_scan(int v, int *sm, int *total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   int x = v;
@@ -26,20 +29,14 @@ __device__ int block_excl_scan(int v, int *sm, int *total) {
   }
   if (lane == 63) sm[w] = x;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int i = 0; i < nw; ++i) {
-      int t = sm[i];
-      sm[i] = acc;
-      acc += t;
-    }
-    sm[nw] = acc;
+  int t = lane < nw ? sm[lane] : 0;
+#pragma unroll
+  for (int o = 1; o < NWMAX; o <<= 1) {
+    int y = __shfl_up(t, o, 64);
+    if (lane >= o) t += y;
   }
-  __syncthreads();
-  int res = sm[w] + x - v;
-  *total = sm[nw];
-  __syncthreads();
-  return res;
+  *total = __shfl(t, nw - 1, 64);
+  return (w ? __shfl(t, w - 1, 64) : 0) + x - v;
 }
 
 // Each thread owns a contiguous range of at most SCHED_MAXB beams (so rows
@@ -68,14 +65,14 @@ struct CapSmem {
 // positions of the old order list (orec); nlive = live beams after admission. Leaves cs.sel[b]
 // set for the selected records and writes the new order list to b_order.
 template <int PER>
-__device__ void cap_select(const DevState &st, CapSmem &cs, int *sm, const int *inp, const int *stp,
+__device__ void cap_select(const DevState &st, CapSmem &cs, int (*sm)[NWMAX], const int *inp, const int *stp,
                            const uint32_t *amask, const int *orec, int b0, int nb, int nlive) {
   // Kept positions are compacted in order ahead of the admitted beams.
   int kept_l = 0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) kept_l += u < nb && orec[u] >= 0;
   int kept_tot;
-  int pos = block_excl_scan(kept_l, sm, &kept_tot);
+  int pos = block_excl_scan(kept_l, sm[0], &kept_tot);
 #pragma unroll
   for (int u = 0; u < PER; ++u)
     if (u < nb && orec[u] >= 0) cs.ord[pos++] = orec[u];
@@ -113,7 +110,7 @@ __device__ void cap_select(const DevState &st, CapSmem &cs, int *sm, const int *
   int hsum = 0;
   for (int j = j0; j < j1; ++j) hsum += cs.hist[j];
   int htot;
-  int cum = block_excl_scan(hsum, sm, &htot);
+  int cum = block_excl_scan(hsum, sm[1], &htot);
   for (int j = j0; j < j1; ++j) {
     const int h = cs.hist[j];
     if (cum <= budget && cum + h > budget) {
@@ -130,7 +127,7 @@ __device__ void cap_select(const DevState &st, CapSmem &cs, int *sm, const int *
   for (int u = 0; u < PER; ++u)
     if (orid[u] >= 0 && (oinfo[u] >> 8) == lstar) lv += oinfo[u] & 0xff;
   int ltot;
-  int e = block_excl_scan(lv, sm, &ltot);
+  int e = block_excl_scan(lv, sm[2], &ltot);
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     if (orid[u] >= 0) {
@@ -146,23 +143,36 @@ __device__ void cap_select(const DevState &st, CapSmem &cs, int *sm, const int *
   __syncthreads();
 }
 
+// A beam's entry for the row list: its first row (-1: not selected), its
+// steps and active mask (steps << 16 | mask), its input and its L_x.
+struct BeamRows {
+  int row0;
+  uint32_t info;
+  int input, lx;
+};
+
 // The scheduler proper. PER = beams per thread (a contiguous range, so rows
-// come out in beam order). Every beam and slot field it needs is loaded at
-// the start in one batch; the step then takes two barrier phases (plus the
-// capacity selection's): live/free counts with the minimal l_t, then the
-// row offsets with the step's totals.
+// come out in beam order). Every beam field it needs is loaded at the start
+// in one batch (a beam's candidates as one mask word, written by the beam
+// update); the step then takes two scans (plus the capacity selection's):
+// live/free counts with the minimal l_t, then the row offsets with the
+// step's totals. The row list is written from LDS with consecutive threads on
+// consecutive slots, whose last tokens were loaded at the start the same way:
+// with each thread reading and writing its own beams' slots one by one, 2048
+// records of k = 5 took 21.4 us, now 12.9 (128 records, where the chain of
+// loads and scans sets the time: 4.9 and 5.0).
 template <int PER>
 __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
-  constexpr int NWMAX = SCHED_THREADS / 64;
   const int NW = (int)blockDim.x >> 6;
-  __shared__ long long ph1[NWMAX + 1];
-  __shared__ int ph1_min[NWMAX + 1];
-  __shared__ int ph2[4][NWMAX + 1];
-  __shared__ int sm[NWMAX + 1];
+  __shared__ long long ph1[NWMAX];
+  __shared__ int ph1_min[NWMAX];
+  __shared__ int ph2[4][NWMAX];
+  __shared__ int sm[3][NWMAX];
   __shared__ CapSmem cs;
+  __shared__ BeamRows br[SCHED_MAXP];
   DevCtrl *c = st.ctrl;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int n = st.n, k = st.k;
+  const int n = st.n, k = st.k, nslots = n * k;
   const int nq = c->n_queued, cursor = c->cursor;
   const int b0 = min(n, tid * PER), nb = min(n, b0 + PER) - b0;
   const bool cap = st.cap != 0;
@@ -188,36 +198,35 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     }
   }
 
-  // Beam records, slot states (active / terminated masks), the inputs'
-  // source lengths and, with at most two beams per thread, the slots' last
-  // tokens. The slot loops run to the compile-time bound so that all loads
-  // are in flight together.
-  constexpr int PT = PER <= 2 ? PER : 1;
+  // Beam records.
   int inp[PER], stp[PER], lxv[PER];
   uint32_t amask[PER], tmask[PER];
-  int tok[PT][KMAX_SUPPORTED];
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     inp[u] = -1;
-    stp[u] = 0;
-    amask[u] = 0u;
-    tmask[u] = 0u;
+    stp[u] = lxv[u] = 0;
+    amask[u] = tmask[u] = 0u;
     if (u < nb) {
       inp[u] = st.b_input[b0 + u];
       stp[u] = st.b_steps[b0 + u];
-#pragma unroll
-      for (int j = 0; j < KMAX_SUPPORTED; ++j) {
-        if (j < k) {
-          const int status = st.s_status[(b0 + u) * k + j];
-          amask[u] |= (uint32_t)(status == SLOT_ACTIVE) << j;
-          tmask[u] |= (uint32_t)(status == SLOT_EOS || status == SLOT_MAXLEN) << j;
-          if (u < PT) tok[u < PT ? u : 0][j] = st.s_tok[(b0 + u) * k + j];
-        }
-      }
+      lxv[u] = st.b_Lx[b0 + u];
+      const uint32_t m = st.b_mask[b0 + u];
+      amask[u] = m & 0xFFFFu;
+      tmask[u] = m >> 16;
     }
   }
+  // Last tokens of slots tid, tid + blockDim, ... (with more beams per thread
+  // than two, loaded when the rows are written).
+  constexpr int PT = PER <= 2 ? PER * KMAX_SUPPORTED : 1;
+  int tok[PT];
+  if constexpr (PER <= 2) {
 #pragma unroll
-  for (int u = 0; u < PER; ++u) lxv[u] = inp[u] >= 0 ? st.q_Lx[inp[u]] : 0;
+    for (int i = 0; i < PT; ++i)
+      tok[i] = i * (int)blockDim.x < nslots ? st.s_tok[min(tid + i * (int)blockDim.x, nslots - 1)] : 0;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (inp[u] < 0) amask[u] = tmask[u] = 0u;
 
   // Phase 1: live (low word) and free (high word) records, exclusive over
   // threads, and the minimal l_t of the live beams.
@@ -243,22 +252,17 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     if (lane == 63) ph1[w] = x;
     if (lane == 0) ph1_min[w] = mm;
     __syncthreads();
-    if (tid == 0) {
-      long long acc = 0;
-      int m = INT_MAX;
-      for (int i = 0; i < NW; ++i) {
-        const long long t = ph1[i];
-        ph1[i] = acc;
-        acc += t;
-        m = min(m, ph1_min[i]);
-      }
-      ph1[NW] = acc;
-      ph1_min[NW] = m;
+    long long t = lane < NW ? ph1[lane] : 0;
+    mn0 = lane < NW ? ph1_min[lane] : INT_MAX;
+#pragma unroll
+    for (int o = 1; o < NWMAX; o <<= 1) {
+      const long long y = __shfl_up(t, o, 64);
+      if (lane >= o) t += y;
+      mn0 = min(mn0, __shfl_xor(mn0, o, 64));
     }
-    __syncthreads();
-    pre = ph1[w] + x - v;
-    tot = ph1[NW];
-    mn0 = ph1_min[NW];
+    tot = __shfl(t, NW - 1, 64);
+    mn0 = __shfl(mn0, 0, 64);
+    pre = (w ? __shfl(t, w - 1, 64) : 0) + x - v;
   }
   const int live = (int)(tot & 0xffffffff);
 
@@ -279,8 +283,9 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
           amask[u] = 1u;
           tmask[u] = 0u;
           lxv[u] = st.q_Lx[inp[u]];
-          if (u < PT) tok[u < PT ? u : 0][0] = 0;
           st.b_input[b] = inp[u];
+          st.b_mask[b] = 1u;
+          st.b_Lx[b] = lxv[u];
           st.b_steps[b] = 0;
           st.b_par[b] = 0;
           st.b_ml[b] = st.q_ml[inp[u]];
@@ -289,7 +294,6 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
           for (int j = 0; j < k; ++j) {
             st.s_status[b * k + j] = j == 0 ? SLOT_ACTIVE : SLOT_EMPTY;
             st.s_score[b * k + j] = 0.0;
-            st.s_tok[b * k + j] = 0;   // start symbol
           }
         }
         ++rank;
@@ -338,59 +342,59 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
       ph2[3][w] = q;
     }
     __syncthreads();
-    if (tid == 0) {
-      int acc = 0, ta = 0, tb = 0, tq = 0;
-      for (int i = 0; i < NW; ++i) {
-        const int t = ph2[0][i];
-        ph2[0][i] = acc;
-        acc += t;
-        ta += ph2[1][i];
-        tb += ph2[2][i];
-        tq += ph2[3][i];
-      }
-      ph2[0][NW] = acc;
-      ph2[1][NW] = ta;
-      ph2[2][NW] = tb;
-      ph2[3][NW] = tq;
+    // Lanes 0..15: the waves' row counts, scanned; 16..31, 32..47, 48..63: the
+    // three totals.
+    int t = (lane & 15) < NW ? ph2[lane >> 4][lane & 15] : 0;
+#pragma unroll
+    for (int o = 1; o < NWMAX; o <<= 1) {
+      const int y = __shfl_up(t, o, 64);
+      if ((lane & 15) >= o) t += y;
     }
-    __syncthreads();
-    row = ph2[0][w] + x - act_l;
-    R = ph2[0][NW];
-    noops = ph2[1][NW];
-    nsel = ph2[2][NW];
-    npos = ph2[3][NW];
+    row = (w ? __shfl(t, w - 1, 64) : 0) + x - act_l;
+    R = __shfl(t, NWMAX - 1, 64);
+    noops = __shfl(t, 2 * NWMAX - 1, 64);
+    nsel = __shfl(t, 3 * NWMAX - 1, 64);
+    npos = __shfl(t, 4 * NWMAX - 1, 64);
   }
+  static_assert(4 * NWMAX == 64, "one lane per (quantity, wave)");
 
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     if (u < nb) {
-      const int b = b0 + u;
-      st.b_sel[b] = sel[u];
-      const int lx = sel[u] ? lxv[u] : 0;
-#pragma unroll
-      for (int j = 0; j < KMAX_SUPPORTED; ++j) {
-        if (j >= k) break;
-        const int s = b * k + j;
-        if ((amask[u] >> j) & 1u) {
-          int y;
-          if (u < PT) y = tok[u < PT ? u : 0][j];
-          else y = st.s_tok[s];
-          st.r_slot[row] = s;
-          st.r_hsrc[row] = stp[u] == 0 ? -1 - inp[u] : s;   // a fresh beam reads its encoding h0
-          if (st.rec_i8) {
-            st.haux[row].F = 1;
-            st.haux[row].n = 0;
-          }
-          st.r_y[row] = y;
-          st.r_t[row] = stp[u] + 1;
-          st.r_Lx[row] = lx;
-          st.s_row[s] = row;
-          ++row;
-        } else {
-          st.s_row[s] = -1;
-        }
-      }
+      const int r0 = sel[u] ? row : -1;
+      st.b_row0[b0 + u] = r0;
+      br[b0 + u] = BeamRows{r0, (uint32_t)stp[u] << 16 | amask[u], inp[u], lxv[u]};
+      row += __popc(amask[u]);
     }
+  }
+  __syncthreads();
+  // The row list: thread per slot.
+  const uint32_t inv = k > 1 ? 0xFFFFFFFFu / (uint32_t)k + 1u : 0u;   // s / k = umulhi(s, inv) for s < 2^16
+  auto emit = [&](int s, int y) {
+    const int b = k > 1 ? (int)__umulhi((uint32_t)s, inv) : s, j = s - b * k;
+    const BeamRows x = br[b];
+    if (x.row0 < 0 || !((x.info >> j) & 1u)) return;
+    const int r = x.row0 + __popc(x.info & ((1u << j) - 1u));
+    const int steps = (int)(x.info >> 16);
+    st.r_slot[r] = s;
+    st.r_hsrc[r] = steps == 0 ? -1 - x.input : s;   // a fresh beam reads its encoding h0
+    st.r_y[r] = steps == 0 ? 0 : y;                 // and the start symbol
+    st.r_t[r] = steps + 1;
+    st.r_Lx[r] = x.lx;
+    if (st.rec_i8) {
+      st.haux[r].F = 1;
+      st.haux[r].n = 0;
+    }
+  };
+  if constexpr (PER <= 2) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int s = tid + i * (int)blockDim.x;
+      if (s >= nslots) break;
+      emit(s, tok[i]);
+    }
+  } else {
+    for (int s = tid; s < nslots; s += (int)blockDim.x) emit(s, st.s_tok[s]);
   }
 
   if (tid == 0) {
@@ -422,13 +426,13 @@ __global__ void k_init(DevState st) {
   if (i < st.n) {
     st.b_input[i] = -1;
     st.b_steps[i] = 0;
-    st.b_sel[i] = 0;
+    st.b_row0[i] = -1;
+    st.b_mask[i] = 0u;
     st.b_par[i] = 0;
     st.b_nout[i] = 0;
   }
   if (i < st.n * st.k) {
     st.s_status[i] = SLOT_EMPTY;
-    st.s_row[i] = -1;
   }
   if (i < st.max_inputs) st.o_count[i] = 0;
   if (i == 0) {

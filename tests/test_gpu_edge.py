@@ -207,3 +207,14 @@ def test_small_vocabulary_beams(gpu, V, k, sched):
     wl = make_workload(scaled(1, N=40, n=6, V=V, k=k, M=max(1, k - 1)))
     print(f"[parity] small vocabulary V={V} k={k} {sched}", flush=True)
     check_parity(wl, sched, pool=12 if sched == "var_cap" else None)
+
+
+@pytest.mark.parametrize("n,k,sched", [(63, 3, "var_stream"), (64, 16, "var_fifo"), (65, 1, "var_cap"),
+                                       (1025, 2, "var_stream"), (700, 3, "var_cap"), (2100, 1, "var_fifo")])
+def test_scheduler_row_lists(gpu, n, k, sched):
+    """Row lists over one, two and four beam records per scheduler thread, with
+    widths that do not divide the slots."""
+    N = min(3 * n, 2600)
+    wl = make_workload(scaled(1, N=N, n=n, V=130, k=k, M=k, len_hi=8, max_len=12))
+    print(f"[parity] row lists n={n} k={k} {sched}", flush=True)
+    check_parity(wl, sched, pool=2 * n if sched == "var_cap" else None)
