@@ -177,17 +177,21 @@ __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row,
 // 128-token tile) are recomputed from W_out, all their logits enter the
 // lists in place of the record's keys, and the k keys are drawn again. Any
 // other tile's unkept keys rank below its last kept key, so at most at the
-// k-th key drawn, and adding candidates can only raise the k-th key.
+// k-th key drawn, and adding candidates can only raise the k-th key. With
+// short tile lists a lane's list is 8 keys for every k > 4 (a lane rarely
+// holds more than 8 of a row's best 16), and a lane whose 8th key ranks above
+// the k-th key drawn sends the row the same way, on lists of KB keys.
 // (With full lists, TK = KB >= k, no tile can hold more of the best k.)
 template <int KB, int TK, int G>
 __device__ __forceinline__ double merge_row(const DevState &st, int row, int lane, int k, cand_key &mine) {
   constexpr int PW = part_width(TK);
+  constexpr int LB = TK == TILE_KEYS_SHORT && KB > 8 ? 8 : KB;   // keys of a lane's list
   // Partials in flight per lane (full-length lists come with fewer than 64
   // tiles, one per lane).
   constexpr int NBT = TK == TILE_KEYS_SHORT && G == 64 ? 4 : 1;
   const float *base = st.part + (size_t)row * st.S * PW;
   float m = -INFINITY, s = 0.0f;
-  TopK<KB> tk;
+  TopK<LB> tk;
   topk_init(tk);
   cand_key last_max = 0ull;   // largest last kept key over the lane's tiles
 #pragma unroll 1
@@ -219,8 +223,8 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
         if (ok) lse_merge(m, s, rec[u][0], rec[u][1]);
         last_max = run[u].k[3] > last_max ? run[u].k[3] : last_max;
       }
-      TopK<KB> batch;
-      if constexpr (KB == 4) {
+      TopK<LB> batch;
+      if constexpr (LB == 4) {
         topk_merge(run[0], run[1]);
         topk_merge(run[2], run[3]);
         topk_merge(run[0], run[2]);
@@ -229,18 +233,14 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
         cand_key a8[8], b8[8];
         merge_sorted<4>(run[0].k, run[1].k, a8);
         merge_sorted<4>(run[2].k, run[3].k, b8);
-        if constexpr (KB == 8) {
-          TopK<8> x, y;
+        TopK<8> x, y;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            x.k[j] = a8[j];
-            y.k[j] = b8[j];
-          }
-          topk_merge(x, y);
-          batch = x;
-        } else {
-          merge_sorted<8>(a8, b8, batch.k);
+        for (int j = 0; j < 8; ++j) {
+          x.k[j] = a8[j];
+          y.k[j] = b8[j];
         }
+        topk_merge(x, y);
+        batch = x;
       }
       if (t0 == lane) tk = batch;
       else topk_merge(tk, batch);
@@ -250,7 +250,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
         if (t0 + G * u < st.S) {
           TopK<TK> t4;
           topk_load(t4, rec[u] + 2);
-          TopK<KB> o;
+          TopK<LB> o;
           topk_init(o);
 #pragma unroll
           for (int j = 0; j < TK; ++j) o.k[j] = t4.k[j];
@@ -262,6 +262,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
     }
   }
   group_lse<G>(m, s);
+  if constexpr (LB < KB) last_max = tk.k[LB - 1] > last_max ? tk.k[LB - 1] : last_max;
   cand_key kth = 0ull;
   mine = 0ull;
 #pragma unroll 1
@@ -271,8 +272,8 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
     kth = best;
     if (tk.k[0] == best) {
 #pragma unroll
-      for (int j = 0; j + 1 < KB; ++j) tk.k[j] = tk.k[j + 1];
-      tk.k[KB - 1] = 0ull;
+      for (int j = 0; j + 1 < LB; ++j) tk.k[j] = tk.k[j + 1];
+      tk.k[LB - 1] = 0ull;
     }
   }
   // The row's log-sum-exp as lane 0 has it, for every lane.
@@ -280,7 +281,8 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
   if (G < 64 || __ballot(last_max > kth) == 0ull) return lse;
 
   // Rare path: rebuild the lists with the saturated tiles recomputed.
-  topk_init(tk);
+  TopK<KB> all;
+  topk_init(all);
   for (int t0 = 0; t0 < st.S; t0 += 64) {
     const int t = t0 + lane;
     bool sat = false;
@@ -294,7 +296,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
         topk_init(oo);
 #pragma unroll
         for (int j = 0; j < TK; ++j) oo.k[j] = o.k[j];
-        topk_merge(tk, oo);
+        topk_merge(all, oo);
       }
     }
     unsigned long long mask = __ballot(sat);
@@ -305,19 +307,19 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
       const int src = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
       const int vt = t0 + src;
-      if (st.dtype == 1) recompute_tile_bf16<KB>(st, row, vt, lane, tk);
-      else recompute_tile_f32<KB>(st, row, vt, lane, tk);
+      if (st.dtype == 1) recompute_tile_bf16<KB>(st, row, vt, lane, all);
+      else recompute_tile_f32<KB>(st, row, vt, lane, all);
     }
   }
   mine = 0ull;
 #pragma unroll 1
   for (int r = 0; r < k; ++r) {
-    const cand_key best = group_max_key<G>(tk.k[0]);
+    const cand_key best = group_max_key<G>(all.k[0]);
     if (lane == r) mine = best;
-    if (tk.k[0] == best) {
+    if (all.k[0] == best) {
 #pragma unroll
-      for (int j = 0; j + 1 < KB; ++j) tk.k[j] = tk.k[j + 1];
-      tk.k[KB - 1] = 0ull;
+      for (int j = 0; j + 1 < KB; ++j) all.k[j] = all.k[j + 1];
+      all.k[KB - 1] = 0ull;
     }
   }
   return lse;
@@ -443,9 +445,9 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
 
   // Ranking of all expansions (key: score, parent rank, token; Sec. 2):
   // thread c < C holds candidate c (parent c / KC's child c % KC, or, paper
-  // rule, the no-op of terminated parent c - k KC) and counts the valid
-  // candidates that rank above it; that count is its rank, all keys being
-  // distinct. Ranks below RM (k, or 2k under the Fairseq rule) are kept.
+  // rule, the no-op of terminated parent c - k KC); a candidate's rank is
+  // the count of candidates that rank above it, all keys being distinct.
+  // Ranks below RM (k, or 2k under the Fairseq rule) are kept.
   const int NCL = k * KC;
   const int C = NCL + (fairseq ? 0 : k);
   const int RM = fairseq ? 2 * k : k;
@@ -475,18 +477,44 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   const int C8 = (C + 7) & ~7;
   if (tid < C8) cand[tid] = Cand{cs, ck, 0};
   const int nvalid = __syncthreads_count(cv);
-  if (cv) {
-    int rank = 0;
-    for (int c0 = 0; c0 < C8; c0 += 8) {
-      Cand o[8];
+  if constexpr (NT == BEAM_THREADS) {
+    // CP threads per candidate (as many as there are, up to 16) compare it with
+    // every CP-th of the others and add up.
+    const int CP = NT >= 16 * C8 ? 16 : NT >= 8 * C8 ? 8 : NT >= 4 * C8 ? 4 : NT >= 2 * C8 ? 2 : 1;
+    if (tid < CP * C8) {
+      const int me = tid / CP, part = tid - me * CP;
+      const Cand mine = cand[me];
+      int rank = 0;
+      for (int c0 = part; c0 < C8; c0 += 8 * CP) {
+        Cand o[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) o[u] = cand[c0 + u];
+        for (int u = 0; u < 8; ++u) o[u] = cand[min(c0 + u * CP, C8 - 1)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) rank += ranks_above(o[u].score, o[u].key, cs, ck) ? 1 : 0;
+        for (int u = 0; u < 8; ++u) rank += c0 + u * CP < C8 && ranks_above(o[u].score, o[u].key, mine.score, mine.key) ? 1 : 0;
+      }
+      if (CP > 1) rank += (int)dpp_partner<0>((uint32_t)rank);
+      if (CP > 2) rank += (int)dpp_partner<1>((uint32_t)rank);
+      if (CP > 4) rank += (int)dpp_partner<2>((uint32_t)rank);
+      if (CP > 8) rank += (int)dpp_partner<3>((uint32_t)rank);
+      if (part == 0 && mine.key != NO_KEY && rank < RM) {
+        r_score[rank] = mine.score;
+        r_key[rank] = mine.key;
+      }
     }
-    if (rank < RM) {
-      r_score[rank] = cs;
-      r_key[rank] = ck;
+  } else {
+    if (cv) {
+      int rank = 0;
+      for (int c0 = 0; c0 < C8; c0 += 8) {
+        Cand o[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) o[u] = cand[c0 + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += ranks_above(o[u].score, o[u].key, cs, ck) ? 1 : 0;
+      }
+      if (rank < RM) {
+        r_score[rank] = cs;
+        r_key[rank] = ck;
+      }
     }
   }
   __syncthreads();
@@ -654,30 +682,76 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     st.b_par[b] ^= 1;
     st.b_nout[b] = nout0 + no;
   }
-  // State copy: s_h[rank] <- hbuf[row(parent)] for every active survivor,
-  // flattened over (survivor, 16-byte chunk) so all threads stream.
-  const int rowbytes = st.d * (st.dtype == 1 ? 2 : 4);
-  const int chunks = rowbytes / 16;
-  const uint4 *__restrict__ hb = static_cast<const uint4 *>(st.hbuf);
-  uint4 *__restrict__ sh = static_cast<uint4 *>(st.s_h);
-  const int total = w * chunks;
-  for (int x = tid; x < total; x += NT) {
-    const int r = x / chunks, c = x - r * chunks;
-    if (nstat[r] == SLOT_ACTIVE) sh[(size_t)(base + r) * chunks + c] = hb[(size_t)sl_row[npar[r]] * chunks + c];
-  }
-  // The state's digit planes and list, for the exact bf16 recurrence.
-  if (st.rec_i8) {
-    const int dch = (int)(rec_dig_row_bytes(st.d) / 16), ach = (int)(sizeof(RowAux) / 16), tch = dch + ach;
-    const uint4 *__restrict__ hd = reinterpret_cast<const uint4 *>(st.hd);
-    uint4 *__restrict__ shd = reinterpret_cast<uint4 *>(st.s_hd);
-    const uint4 *__restrict__ ha = reinterpret_cast<const uint4 *>(st.haux);
-    uint4 *__restrict__ sha = reinterpret_cast<uint4 *>(st.s_haux);
-    for (int x = tid; x < w * tch; x += NT) {
-      const int r = x / tch, c = x - r * tch;
-      if (nstat[r] != SLOT_ACTIVE) continue;
-      const size_t src = sl_row[npar[r]];
-      if (c < dch) shd[(size_t)(base + r) * dch + c] = hd[src * dch + c];
-      else sha[(size_t)(base + r) * ach + (c - dch)] = ha[src * ach + (c - dch)];
+  // State copy: s_h[rank] <- hbuf[row(parent)] for every active survivor, with
+  // the digit planes and list of the exact bf16 recurrence.
+  if constexpr (NT == BEAM_THREADS) {
+    // A thread takes one 16-byte chunk of several survivors (spread over
+    // groups of threads when a state has fewer chunks than the workgroup
+    // threads) and loads them all, without branches, before it stores the
+    // first: 128 beams, |V| = 32000, bf16, k = 10: 22.8 -> 21.6 us per
+    // timestep. Beams of one wave lose by it (k = 4: 7.1 -> 7.8 us).
+    const int hch = st.d * (st.dtype == 1 ? 2 : 4) / 16;
+    const int dch = st.rec_i8 ? (int)(rec_dig_row_bytes(st.d) / 16) : 0, ach = st.rec_i8 ? (int)(sizeof(RowAux) / 16) : 0;
+    const int tot = hch + dch + ach;
+    const int groups = max(1, NT / tot), grp = groups > 1 ? tid / tot : 0;
+    constexpr int U = 8;
+    if (grp < groups) {
+      for (int c = tid - grp * tot; c < tot; c += groups > 1 ? tot : NT) {
+        const uint4 *src;
+        uint4 *dst;
+        int ch;   // chunks per row of this array
+        if (c < hch) {
+          src = static_cast<const uint4 *>(st.hbuf) + c;
+          dst = static_cast<uint4 *>(st.s_h) + c;
+          ch = hch;
+        } else if (c < hch + dch) {
+          src = reinterpret_cast<const uint4 *>(st.hd) + (c - hch);
+          dst = reinterpret_cast<uint4 *>(st.s_hd) + (c - hch);
+          ch = dch;
+        } else {
+          src = reinterpret_cast<const uint4 *>(st.haux) + (c - hch - dch);
+          dst = reinterpret_cast<uint4 *>(st.s_haux) + (c - hch - dch);
+          ch = ach;
+        }
+        for (int r0 = grp; r0 < w; r0 += U * groups) {
+          uint4 v[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int r = min(r0 + u * groups, w - 1);
+            v[u] = nstat[r] == SLOT_ACTIVE ? src[(size_t)sl_row[npar[r]] * ch] : uint4{0u, 0u, 0u, 0u};
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * groups;
+            if (r < w && nstat[r] == SLOT_ACTIVE) dst[(size_t)(base + r) * ch] = v[u];
+          }
+        }
+      }
+    }
+  } else {
+    const int rowbytes = st.d * (st.dtype == 1 ? 2 : 4);
+    const int chunks = rowbytes / 16;
+    const uint4 *__restrict__ hb = static_cast<const uint4 *>(st.hbuf);
+    uint4 *__restrict__ sh = static_cast<uint4 *>(st.s_h);
+    const int total = w * chunks;
+    for (int x = tid; x < total; x += NT) {
+      const int r = x / chunks, c = x - r * chunks;
+      if (nstat[r] == SLOT_ACTIVE) sh[(size_t)(base + r) * chunks + c] = hb[(size_t)sl_row[npar[r]] * chunks + c];
+    }
+    // The state's digit planes and list, for the exact bf16 recurrence.
+    if (st.rec_i8) {
+      const int dch = (int)(rec_dig_row_bytes(st.d) / 16), ach = (int)(sizeof(RowAux) / 16), tch = dch + ach;
+      const uint4 *__restrict__ hd = reinterpret_cast<const uint4 *>(st.hd);
+      uint4 *__restrict__ shd = reinterpret_cast<uint4 *>(st.s_hd);
+      const uint4 *__restrict__ ha = reinterpret_cast<const uint4 *>(st.haux);
+      uint4 *__restrict__ sha = reinterpret_cast<uint4 *>(st.s_haux);
+      for (int x = tid; x < w * tch; x += NT) {
+        const int r = x / tch, c = x - r * tch;
+        if (nstat[r] != SLOT_ACTIVE) continue;
+        const size_t src = sl_row[npar[r]];
+        if (c < dch) shd[(size_t)(base + r) * dch + c] = hd[src * dch + c];
+        else sha[(size_t)(base + r) * ach + (c - dch)] = ha[src * ach + (c - dch)];
+      }
     }
   }
   // KV state: an active child's ancestors are its parent's (levels 0 .. t-2)

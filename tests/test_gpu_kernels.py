@@ -249,3 +249,24 @@ def test_expand_state_buffers(gpu, cfg_i, form):
     assert torch.equal(got[0], want[0])
     for g, w in zip(got[1:], want[1:]):
         assert np.array_equal(g, w)
+
+
+@pytest.mark.parametrize("cfg_i,k,per_tile", [(4, 16, 3), (1, 16, 3), (4, 9, 3), (1, 12, 4)])
+def test_expand_one_lane_holds_the_best(gpu, cfg_i, k, per_tile):
+    """Tiles t, t + 64, t + 128, t + 192 are merged by one lane, which keeps 8
+    keys; here they hold 12 or 16 of a row's best tokens (with 4 in a tile the
+    tile's short list may hide more as well)."""
+    wl = make_workload(scaled(cfg_i, N=4, V=32000, d=128, k=k, M=4, n=4))
+    rng = np.random.default_rng(71)
+    u = rng.choice([-1.0, 1.0], 128)
+    E = wl.E * 0.1 + 0.5 * u
+    W = wl.W_out.copy()
+    toks = [128 * (5 + 64 * i) + 7 * j + 3 for i in range(4) for j in range(per_tile)]
+    for x, v in enumerate(toks):
+        W[v] = u * (0.05 + 0.002 * ((5 * x) % len(toks)))
+    cast = _bf16 if wl.is_bf16 else (lambda a: a.astype(np.float32))
+    wl = dataclasses.replace(wl, E=cast(E), W_out=cast(W))
+    _, _, _, _, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, 37, 72)
+    print(f"[expand] one lane {wl.cfg.dtype} k={k}", flush=True)
+    assert len(set(tok[0].tolist()) & set(toks)) >= min(k, len(toks)) - 1
+    _check_rows(wl, h_gpu, lp, tok, h_ref, lp_ref, lse)
