@@ -779,40 +779,67 @@ __global__ __launch_bounds__(RTHREADS_I8, 2) void k_rec_i8(DevState st) {
   }
 }
 
-// Digits of `count` bf16 rows [count][d] (one workgroup per row): the row
-// exponent, the three planes and the list of values below the window.
-__global__ __launch_bounds__(256) void k_row_digits(const uint16_t *__restrict__ rows, int count, int d,
-                                                    int8_t *__restrict__ dig, RowAux *__restrict__ aux) {
-  const int r = blockIdx.x;
-  if (r >= count) return;
-  const uint16_t *x = rows + (size_t)r * d;
-  __shared__ int smx, sn;
-  if (threadIdx.x == 0) {
-    smx = 1;
-    sn = 0;
-  }
+// Digits of `count` bf16 rows [count][d] (one wave per row, 16 values per
+// lane and turn): the row exponent, the three planes and the list of values
+// below the window. Bound by memory (a row is read twice, the second time
+// from cache); with 2-byte loads and 1-byte stores, a workgroup per row, d =
+// 1024, 5120 rows took 22.8 us and 389 rows 6.2, now 11.4 and 5.4.
+constexpr int DIGIT_WAVES = 4;
+__global__ __launch_bounds__(64 * DIGIT_WAVES) void k_row_digits(const uint16_t *__restrict__ rows, int count, int d,
+                                                                 int8_t *__restrict__ dig, RowAux *__restrict__ aux) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = blockIdx.x * DIGIT_WAVES + w;
+  __shared__ int sn[DIGIT_WAVES];
+  if (lane == 0) sn[w] = 0;
   __syncthreads();
-  atomicMax(&smx, bf16_max_eu(x, threadIdx.x, d, blockDim.x));
-  __syncthreads();
-  const int E = smx - 126;
-  int8_t *dr = dig + (size_t)r * rec_dig_row_bytes(d);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    int a0, a1, a2;
-    if (!bf16_digits3(x[i], E, a0, a1, a2)) {
-      const int k = atomicAdd(&sn, 1);
-      if (k < REC_HL) {
-        aux[r].col[k] = i;
-        aux[r].val[k] = bf16f(x[i]);
-      }
+  int E = 0;
+  if (r < count) {
+    const uint16_t *x = rows + (size_t)r * d;   // 256-byte rows or larger (d a multiple of 256): 16-byte aligned
+    uint32_t mx = 1u;
+    for (int i = lane * 16; i < d; i += 64 * 16) {
+      union {
+        u4 u[2];
+        uint16_t h[16];
+      } v;
+      v.u[0] = *reinterpret_cast<const u4 *>(x + i);
+      v.u[1] = *reinterpret_cast<const u4 *>(x + i + 8);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) mx = max(mx, ((uint32_t)v.h[q] >> 7) & 0xFFu);
     }
-    dr[rec_dig_off(i, 0)] = (int8_t)a0;
-    dr[rec_dig_off(i, 1)] = (int8_t)a1;
-    dr[rec_dig_off(i, 2)] = (int8_t)a2;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
+    E = (int)mx - 126;
+    int8_t *dr = dig + (size_t)r * rec_dig_row_bytes(d);
+    for (int i = lane * 16; i < d; i += 64 * 16) {
+      union {
+        u4 u[2];
+        uint16_t h[16];
+      } v;
+      v.u[0] = *reinterpret_cast<const u4 *>(x + i);
+      v.u[1] = *reinterpret_cast<const u4 *>(x + i + 8);
+      uint32_t word[3][4] = {};
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        int dg[3];
+        if (!bf16_digits3(v.h[q], E, dg[0], dg[1], dg[2])) {
+          const int k = atomicAdd(&sn[w], 1);
+          if (k < REC_HL) {
+            aux[r].col[k] = i + q;
+            aux[r].val[k] = bf16f(v.h[q]);
+          }
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p) word[p][q >> 2] |= (uint32_t)(uint8_t)dg[p] << (8 * (q & 3));
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<u4 *>(dr + rec_dig_off(i, p)) = u4{word[p][0], word[p][1], word[p][2], word[p][3]};
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (r < count && lane == 0) {
     aux[r].F = E;
-    aux[r].n = sn;
+    aux[r].n = sn[w];
   }
 }
 
@@ -967,8 +994,8 @@ hipError_t launch_rec_prepare(const DevState &st, hipStream_t s) {
 hipError_t launch_row_digits(const DevState &st, const void *rows, int count, int8_t *dig, RowAux *aux,
                              hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_row_digits, dim3(count), dim3(256), 0, s, static_cast<const uint16_t *>(rows), count, st.d,
-                     dig, aux);
+  hipLaunchKernelGGL(k_row_digits, dim3((count + DIGIT_WAVES - 1) / DIGIT_WAVES), dim3(64 * DIGIT_WAVES), 0, s,
+                     static_cast<const uint16_t *>(rows), count, st.d, dig, aux);
   return hipGetLastError();
 }
 
