@@ -19,7 +19,9 @@
  *  - The caller owns all device memory (weights, the workspace, h0 staging);
  *    it must outlive the decoder. The library never allocates or frees device
  *    memory; it owns a small host-side object, pinned host staging for the
- *    per-input lengths (8 bytes per queue entry) and a few HIP events. The
+ *    per-input lengths (8 bytes per queue entry) and, from the first
+ *    sb_debug_expand on, for that call's arguments and results, and a few HIP
+ *    events. The
  *    one exception is sb_create_noalloc, whose decoders use a static device
  *    array of the library in place of a caller workspace.
  *  - All device work is ordered on the decoder's stream.
@@ -80,7 +82,9 @@ typedef enum {
 typedef enum { SB_RULE_PAPER = 0, SB_RULE_FAIRSEQ = 1 } sb_rule;
 
 /* Storage type of weights, h0 and decoder states. SB_F32: fp32 everywhere
- * (MFMA fp32, fp32 accumulation). SB_BF16: bf16 weights and states; the
+ * (fp32 accumulation; the recurrence on the fp32 MFMA, the projection's
+ * products from pairs of fp16 values that hold the 24 bits of each operand,
+ * with an error against 64 bits below the fp32 MFMA's). SB_BF16: bf16 weights and states; the
  * projection accumulates in fp32; the recurrence pre-activation is the
  * exact sum of the bf16 products (integer digit products, d a multiple of
  * 256 up to 2048; otherwise, or when W_h has many values far below its
@@ -179,7 +183,9 @@ sb_status sb_validate(const sb_model *model, const sb_params *params);
 sb_status sb_create(const sb_model *model, const sb_params *params, void *workspace,
                     size_t bytes, void *stream, sb_decoder **out);
 
-/* Largest workspace (bytes) a decoder made by sb_create_noalloc can use. */
+/* Largest workspace (bytes) a decoder made by sb_create_noalloc can use, the
+ * fp32 projection's split states and row scales and the beams' L_x not
+ * counted (the static array has room for them behind it). */
 #define SB_NOALLOC_SCRATCH_BYTES (64u << 20)
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -189,7 +195,7 @@ sb_status sb_create(const sb_model *model, const sb_params *params, void *worksp
  * on holds until the process ends, and static host storage for the decoder
  * object; the call makes no device or pinned-host allocation (no hipMalloc,
  * hipHostMalloc, hipFree, event or stream creation).
- *  - Shapes whose workspace (sb_workspace_bytes) exceeds the scratch return
+ *  - Shapes whose workspace exceeds the scratch (counted as above) return
  *    SB_E_WORKSPACE; sb_last_error(NULL) gives the sizes.
  *  - One such decoder per GPU at a time: while one is alive (until
  *    sb_destroy), another call on the same GPU returns SB_E_STATE. The
