@@ -258,6 +258,22 @@ __global__ __launch_bounds__(256) void k_debug_rows(DevState st, const int32_t *
   }
 }
 
+// Whether a kernel of GPU `device` may read and write `bytes` at p as they
+// stand: device memory of that GPU, within one allocation. A copy also takes
+// host memory and other GPUs', and refuses what is out of range.
+bool on_device(const void *p, size_t bytes, int device) {
+  hipPointerAttribute_t a;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == device &&
+         (uintptr_t)p + bytes <= (uintptr_t)base + size;
+}
+
 constexpr int BURST = 8;   // timesteps per graph launch / per done-flag poll
 
 // One timestep of Alg. 1. With e0/e1 given, HIP events bracket the
@@ -875,18 +891,23 @@ sb_status sb_debug_expand(sb_decoder *dec, int32_t R, const void *h_prev, const 
   // them took 95 us next to 20 us of kernels), so the row metadata comes and
   // the results go through one pinned block that the kernels read and write,
   // and the states are used where the caller has them; one wait at the end.
-  // Unaligned or overlapping state buffers, and decoders that allocate
-  // nothing, take copies as before.
+  // State buffers that are unaligned, overlap or are not this GPU's memory, and
+  // decoders that allocate nothing, take copies.
   if (!dec->pinned_dbg && !dec->noalloc) {
     const size_t Rm = st.R_max;
+    // Another thread may be capturing a stream: the allocation is none of its work.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (hipHostMalloc(reinterpret_cast<void **>(&dec->pinned_dbg), Rm * (8 + 8 * k + 4 * k + 12), hipHostMallocDefault) !=
         hipSuccess) {
       dec->pinned_dbg = nullptr;
       (void)hipGetLastError();
     }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
   const uintptr_t pi = (uintptr_t)h_prev, po = (uintptr_t)h_out;
-  const bool in_place = ((pi | po) & 15) == 0 && (pi + bytes <= po || po + bytes <= pi);
+  const bool in_place = ((pi | po) & 15) == 0 && (pi + bytes <= po || po + bytes <= pi) &&
+                        on_device(h_prev, bytes, dec->device) && on_device(h_out, bytes, dec->device);
   DevState ds = st;
   int32_t *in = nullptr;
   if (dec->pinned_dbg) {
@@ -909,13 +930,13 @@ sb_status sb_debug_expand(sb_decoder *dec, int32_t R, const void *h_prev, const 
     ds.hbuf = h_out;
     ds.proj_in = h_out;
   } else {
-    HIPCHK(hipMemcpyAsync(st.s_h, h_prev, bytes, hipMemcpyDeviceToDevice, dec->stream));
+    HIPCHK(hipMemcpyAsync(st.s_h, h_prev, bytes, hipMemcpyDefault, dec->stream));
   }
   if (st.rec_i8) HIPCHK(launch_row_digits(st, ds.s_h, R, st.s_hd, st.s_haux, dec->stream));
   HIPCHK(launch_rec(ds, dec->stream));
   HIPCHK(launch_proj(ds, dec->stream));
   HIPCHK(launch_rowmerge(ds, dec->stream));
-  if (!in_place) HIPCHK(hipMemcpyAsync(h_out, st.hbuf, bytes, hipMemcpyDeviceToDevice, dec->stream));
+  if (!in_place) HIPCHK(hipMemcpyAsync(h_out, st.hbuf, bytes, hipMemcpyDefault, dec->stream));
   if (!in) {
     HIPCHK(hipMemcpyAsync(lse, st.r_lse, 8 * N, hipMemcpyDeviceToHost, dec->stream));
     HIPCHK(hipMemcpyAsync(top_lp, st.top_lp, 8 * N * k, hipMemcpyDeviceToHost, dec->stream));

@@ -209,10 +209,10 @@ def test_expand_tile_heights(gpu, cfg_i, R):
 
 
 @pytest.mark.parametrize("cfg_i", [1, 4])
-@pytest.mark.parametrize("form", ["unaligned", "in_place", "noalloc", "again"])
+@pytest.mark.parametrize("form", ["unaligned", "in_place", "noalloc", "again", "host", "pinned"])
 def test_expand_state_buffers(gpu, cfg_i, form):
     """The step reads and writes the caller's state buffers where it can
-    (16-byte aligned, not overlapping) and copies otherwise; a decoder that
+    (this GPU's memory, 16-byte aligned, not overlapping) and copies otherwise; a decoder that
     allocates nothing copies its small arrays too. Same bits in every form."""
     import ctypes
     import torch
@@ -238,6 +238,10 @@ def test_expand_state_buffers(gpu, cfg_i, form):
                                     tok.ctypes.data_as(I))
         assert s == N.SB_OK
         got = (x, lse, lp, tok)
+    elif form in ("host", "pinned"):
+        x = h.cpu()
+        got = dec.debug_expand(x.pin_memory() if form == "pinned" else x, y, t, lx)
+        got = (got[0].cuda(),) + got[1:]
     elif form == "noalloc":
         nd = decoder_for_workload(wl, max_inputs=4, noalloc=True)
         got = nd.debug_expand(h, y, t, lx)
