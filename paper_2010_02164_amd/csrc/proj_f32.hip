@@ -191,7 +191,9 @@ __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
 // that both factors are normal numbers. Layout: [S][4 slices][d / 64 chunks]
 // [4 steps][hi, lo][64 lanes][8 fp16], lane (h, l) of step s holding
 // k = 64 chunk + 16 s + 8 h .. + 7 of vocabulary row 128 vt + 32 slice + l
-// (zero past V).
+// (zero past V). An infinite value is a low part alone: it then meets only the
+// state's high part (which is not zero for |h| above 2^-39), where the high
+// part's product with a state's low part of zero would be NaN.
 __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
   __shared__ float up[32];
   const int d = st.d, nst = d / 16, tid = threadIdx.x;
@@ -229,7 +231,14 @@ __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
     if (v < st.V) {
       const float *src = W + (size_t)v * d + 16 * s + 8 * (ln >> 5);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) split_f16(src[i] * up[ln & 31], hi.f[i], lo.f[i]);
+      for (int i = 0; i < 8; ++i) {
+        const float x = src[i] * up[ln & 31];
+        split_f16(x, hi.f[i], lo.f[i]);
+        if (fabsf(x) == INFINITY) {
+          hi.f[i] = (_Float16)0.0f;
+          lo.f[i] = (_Float16)x;
+        }
+      }
     }
     unsigned char *dst = st.wout_t + ((size_t)blockIdx.x * nst + s) * (2 * FRAG) + ln * 16;
     *reinterpret_cast<u4 *>(dst) = hi.u;

@@ -199,6 +199,29 @@ def test_expand_f32_row_scales(gpu, V, d, R, k):
     assert np.all(np.diff(lp, axis=1) <= 1e-12)
 
 
+@pytest.mark.parametrize("V,d", [(1000, 64), (8320, 192)])
+def test_expand_f32_infinite_weight(gpu, V, d):
+    """An infinite W_out value whose product is -inf takes its token out of the
+    row's sum and list and changes nothing else (one row: the sign of the
+    state's value there decides); its neighbours have states whose low parts
+    are zero, as a state of +-1 does."""
+    wl = make_workload(scaled(1, N=4, V=V, d=d, k=5, M=5, n=1))
+    E = wl.E.copy()
+    E[:, d // 2] = 40.0   # tanh gives 1 exactly
+    wl = dataclasses.replace(wl, E=E)
+    _, _, _, _, _, _, _, tok0, h_ref, _ = _expand_case(wl, 1, 81)
+    W = wl.W_out.copy()
+    banned = [int(tok0[0, 0]), V - 1]
+    for v, i in zip(banned, (3, d // 2)):
+        W[v, i] = -np.inf * np.sign(h_ref[0, i])
+    wl = dataclasses.replace(wl, W_out=W)
+    _, _, _, _, _, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, 1, 81)
+    print(f"[expand] f32 infinite weight V={V} d={d}", flush=True)
+    assert np.isneginf(lp_ref[0, banned]).all() and not set(banned) & set(tok[0].tolist())
+    assert np.isfinite(lse).all() and np.abs(lp - np.take_along_axis(lp_ref, tok, 1)).max() < 1e-4
+    assert np.array_equal(tok[0], np.argsort(-lp_ref[0], kind="stable")[:5])
+
+
 @pytest.mark.parametrize("cfg_i,R", [(c, R) for c in (1, 4) for R in (1, 33, 65, 97, 129, 257)])
 def test_expand_tile_heights(gpu, cfg_i, R):
     """Row tiles of 1 to 4 blocks with a ragged last block, in both types."""
