@@ -84,82 +84,96 @@ __device__ __forceinline__ void group_lse(float &m, float &s) {
   }
 }
 
-// The 128 logits of vocabulary tile vt for one row, recomputed by the
-// projection's own MFMA sequence so that they equal its logits bit for bit
-// (the MFMA's internal rounding is not modelled, it is replayed). Every
+// The logits of a 32-row slice s of vocabulary tile vt for one row, recomputed
+// by the projection's own MFMA sequence so that they equal its logits bit for
+// bit (the MFMA's internal rounding is not modelled, it is replayed). Every
 // column of the MFMA gets the row's state, so all 32 columns hold the same
-// logits; per 32-row slice s, lane (h, l) with l < 16 inserts the logit of
-// register l, vocabulary row 32s + 8(l/4) + 4h + l%4 of the tile, into its
-// list (each of the 128 logits once).
-template <int KB>
-__device__ __forceinline__ void insert_slice(const DevState &st, const f16v &z, int v0, int lane, float bias,
-                                             TopK<KB> &tk) {
-  const int h = lane >> 5, l32 = lane & 31;
-  if (l32 >= 16) return;
-  float x = 0.0f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (r == l32) x = z[r];
-  const int v = v0 + 8 * (l32 >> 2) + 4 * h + (l32 & 3);
-  if (v == 0) x += bias;
-  if (v < st.V) topk_insert(tk, make_key(x, v));
-}
+// logits. The loops are unrolled no further than the registers of the rest of
+// the row merge reach: few tiles come here.
+constexpr int W_FRAG = 1024;   // bytes of a wave-wide fragment of W_out
 
 // fp32: the split products chunk by chunk, then the row scales.
-template <int KB>
-__device__ __forceinline__ void recompute_tile_f32(const DevState &st, int row, int vt, int lane, TopK<KB> &tk) {
+__device__ __forceinline__ f16v recompute_slice_f32(const DevState &st, int row, int vt, int s, int lane) {
   const int nch = st.d / SPLIT_K;
-  const float bias = st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
   const u4 *x = reinterpret_cast<const u4 *>(st.hsplit + split_state_off(st.d, row, 8 * (lane >> 5)));
+  const u4 *a = reinterpret_cast<const u4 *>(st.wout_t + (size_t)(vt * 4 + s) * nch * SPLIT_CHUNK) + lane;
+  f16v tot = {};
 #pragma unroll 1
-  for (int s = 0; s < 4; ++s) {
-    const u4 *a = reinterpret_cast<const u4 *>(st.wout_t + (size_t)(vt * 4 + s) * nch * SPLIT_CHUNK) + lane;
-    f16v tot = {};
-#pragma unroll 1
-    for (int c = 0; c < nch; ++c) {
-      u4 af[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) af[i] = a[c * (SPLIT_CHUNK / 16) + i * 64];
-      split_chunk(af, x + c * (SPLIT_CHUNK / 16), 64, tot);
-    }
-    const int v0 = vt * 128 + 32 * s;
-    insert_slice(st, SplitScale(st.w_scale + v0 + 4 * (lane >> 5)).apply(tot), v0, lane, bias, tk);
+  for (int c = 0; c < nch; ++c) {
+    f16v cross = {};
+#pragma unroll 2
+    for (int i = 0; i < 4; ++i, a += 2 * W_FRAG / 16, x += 2 * W_FRAG / 16) split_step(a[0], a[64], x[0], x[64], tot, cross);
+    split_flush(cross, tot);
   }
+  return SplitScale(st.w_scale + vt * 128 + 32 * s + 4 * (lane >> 5)).apply(tot);
 }
 
 // bf16: each K half accumulated chunk by chunk and piece by piece, then the
 // halves added once.
-template <int KB>
-__device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row, int vt, int lane, TopK<KB> &tk) {
-  constexpr int CH = 128, FRAG = 1024;
+__device__ __forceinline__ f16v recompute_slice_bf16(const DevState &st, int row, int vt, int s, int lane) {
+  constexpr int CH = 128;
   const int nk = st.d * 2 / CH, nh = nk >> 1;
-  const int h = lane >> 5;
-  const unsigned char *x = static_cast<const unsigned char *>(st.proj_in) + (size_t)row * st.d * 2 + 64 * h;
-  const float bias = st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
+  const unsigned char *x = static_cast<const unsigned char *>(st.proj_in) + (size_t)row * st.d * 2 + 64 * (lane >> 5);
+  const unsigned char *a = st.wout_t + ((size_t)vt * nk * 4 + s) * 4 * W_FRAG + lane * 16;
+  f16v first = {}, acc = {};
+#pragma unroll 1
+  for (int c = 0; c < nk; ++c, a += 16 * W_FRAG, x += CH) {
+    if (c == nh) {
+      first = acc;
+      acc = f16v{};
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const u4 av = *reinterpret_cast<const u4 *>(a + q * W_FRAG);
+      const u4 bv = *reinterpret_cast<const u4 *>(x + 16 * q);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, av), __builtin_bit_cast(bf8, bv), acc, 0, 0,
+                                                    0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) first[r] += acc[r];
+  return first;
+}
+
+// The keys of the tile's 128 logits, to LDS.
+__device__ __forceinline__ void recompute_tile(const DevState &st, int row, int vt, int lane, cand_key *keys) {
+  const int h = lane >> 5, l32 = lane & 31;
 #pragma unroll 1
   for (int s = 0; s < 4; ++s) {
-    f16v half[2];
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      f16v acc = {};
-#pragma unroll 1
-      for (int c = g * nh; c < (g + 1) * nh; ++c) {
-        const unsigned char *a = st.wout_t + ((size_t)(vt * nk + c) * 4 + s) * 4 * FRAG + lane * 16;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const u4 av = *reinterpret_cast<const u4 *>(a + q * FRAG);
-          const u4 bv = *reinterpret_cast<const u4 *>(x + c * CH + 16 * q);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, av), __builtin_bit_cast(bf8, bv), acc,
-                                                        0, 0, 0);
-        }
-      }
-      half[g] = acc;
-    }
     f16v z;
+    if (st.dtype == 1) z = recompute_slice_bf16(st, row, vt, s, lane);
+    else z = recompute_slice_f32(st, row, vt, s, lane);
+    // Lane (h, l) with l < 16: register l, vocabulary row 8 (l / 4) + 4h + l % 4 of the slice.
+    float x = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) z[r] = half[0][r] + half[1][r];
-    insert_slice(st, z, vt * 128 + 32 * s, lane, bias, tk);
+    for (int r = 0; r < 16; ++r)
+      if (r == l32) x = z[r];
+    const int i = 32 * s + 8 * (l32 >> 2) + 4 * h + (l32 & 3), v = vt * 128 + i;
+    if (v == 0) x += st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
+    if (l32 < 16) keys[i] = v < st.V ? make_key(x, v) : 0ull;
   }
+}
+
+// The k best of the row's kept keys, from the records themselves: the largest
+// key below the last one drawn, k times. Lane r < k receives the key of rank r;
+// returns the k-th.
+__device__ __forceinline__ cand_key draw_records(const float *base, int S, int lane, int k, cand_key &mine) {
+  constexpr int PW = part_width(TILE_KEYS_SHORT);
+  cand_key last = ~0ull;
+#pragma unroll 1
+  for (int r = 0; r < k; ++r) {
+    cand_key best = 0ull;
+#pragma unroll 1
+    for (int t = lane; t < S; t += 64) {
+      TopK<TILE_KEYS_SHORT> o;
+      topk_load(o, base + (size_t)t * PW + 2);
+#pragma unroll
+      for (int j = 0; j < TILE_KEYS_SHORT; ++j) best = o.k[j] < last && o.k[j] > best ? o.k[j] : best;
+    }
+    last = group_max_key<64>(best);
+    if (lane == r) mine = last;
+  }
+  return last;
 }
 
 // Merge the per-tile partials of one row by G lanes (a wave, or 8 lanes when
@@ -171,19 +185,21 @@ __device__ __forceinline__ void recompute_tile_bf16(const DevState &st, int row,
 // the lane holding the winner dropping it (keys are distinct: they carry
 // the token). Lane r < k receives the key of rank r.
 //
-// A tile record keeps its TK best keys (TK <= KB). If a tile's last kept
+// A tile record keeps its TK best keys (TK <= KB). With full lists, TK = KB >= k,
+// the k keys drawn are the row's best. With short ones, if a tile's last kept
 // key ranks above the k-th key drawn, the tile may hold further keys of the
-// best k: such tiles (rare: TK of the row's best k - 1 in one
-// 128-token tile) are recomputed from W_out, all their logits enter the
-// lists in place of the record's keys, and the k keys are drawn again. Any
-// other tile's unkept keys rank below its last kept key, so at most at the
-// k-th key drawn, and adding candidates can only raise the k-th key. With
-// short tile lists a lane's list is 8 keys for every k > 4 (a lane rarely
-// holds more than 8 of a row's best 16), and a lane whose 8th key ranks above
-// the k-th key drawn sends the row the same way, on lists of KB keys.
-// (With full lists, TK = KB >= k, no tile can hold more of the best k.)
+// best k (rare: TK of the row's best k - 1 in one 128-token tile; at most
+// (k - 1) / TK tiles, as all their kept keys rank above it): such tiles are
+// recomputed from W_out, and the k best drawn from their logits and the keys
+// drawn before. Any other tile's unkept keys rank below its last kept key, so
+// at most at the k-th key drawn, and more candidates can only raise the k-th.
+// A lane's list is 8 keys for every k > 4 there (a lane rarely holds more than
+// 8 of a row's best 16); where a lane's 8th key ranks above the k-th drawn, the
+// k kept keys are first drawn again from the records.
+constexpr int SAT_MAX = (KMAX_SUPPORTED - 1) / TILE_KEYS_SHORT;
 template <int KB, int TK, int G>
-__device__ __forceinline__ double merge_row(const DevState &st, int row, int lane, int k, cand_key &mine) {
+__device__ __forceinline__ double merge_row(const DevState &st, int row, int lane, int k, cand_key *sat_keys,
+                                            cand_key &mine) {
   constexpr int PW = part_width(TK);
   constexpr int LB = TK == TILE_KEYS_SHORT && KB > 8 ? 8 : KB;   // keys of a lane's list
   // Partials in flight per lane (full-length lists come with fewer than 64
@@ -262,7 +278,7 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
     }
   }
   group_lse<G>(m, s);
-  if constexpr (LB < KB) last_max = tk.k[LB - 1] > last_max ? tk.k[LB - 1] : last_max;
+  const cand_key lane_last = LB < KB ? tk.k[LB - 1] : 0ull;
   cand_key kth = 0ull;
   mine = 0ull;
 #pragma unroll 1
@@ -278,64 +294,58 @@ __device__ __forceinline__ double merge_row(const DevState &st, int row, int lan
   }
   // The row's log-sum-exp as lane 0 has it, for every lane.
   const double lse = __shfl((double)m + log((double)s), 0, G);
-  if (G < 64 || __ballot(last_max > kth) == 0ull) return lse;
-
-  // Rare path: rebuild the lists with the saturated tiles recomputed.
-  TopK<KB> all;
-  topk_init(all);
-  for (int t0 = 0; t0 < st.S; t0 += 64) {
-    const int t = t0 + lane;
-    bool sat = false;
-    if (t < st.S) {
-      const float *p = base + (size_t)t * PW;
+  if constexpr (TK >= KB) return lse;
+  else {
+    static_assert(G == 64 && TK == TILE_KEYS_SHORT, "short lists come with 64 or more tiles");
+    if (__ballot(last_max > kth || lane_last > kth) == 0ull) return lse;
+    if (__ballot(lane_last > kth)) kth = draw_records(base, st.S, lane, k, mine);
+    cand_key own = lane < k ? mine : 0ull;
+    int found = 0;
+#pragma unroll 1
+    for (int t0 = 0; t0 < st.S; t0 += 64) {
+      const int t = t0 + lane;
       TopK<TK> o;
-      topk_load(o, p + 2);
-      sat = o.k[TK - 1] > kth;
-      if (!sat) {
-        TopK<KB> oo;
-        topk_init(oo);
-#pragma unroll
-        for (int j = 0; j < TK; ++j) oo.k[j] = o.k[j];
-        topk_merge(all, oo);
+      topk_load(o, base + (size_t)min(t, st.S - 1) * PW + 2);
+      unsigned long long mask = __ballot(t < st.S && o.k[TK - 1] > kth);
+      if (lane == 0 && mask)
+        atomicAdd(reinterpret_cast<unsigned long long *>(&st.ctrl->tile_recomputes),
+                  (unsigned long long)__popcll(mask));
+#pragma unroll 1
+      for (; mask && found < SAT_MAX; mask &= mask - 1, ++found) {
+        const int vt = t0 + __ffsll((long long)mask) - 1;
+        recompute_tile(st, row, vt, lane, sat_keys + found * 128);
+        if (key_idx(own) >> 7 == vt) own = 0ull;   // among the recomputed
       }
     }
-    unsigned long long mask = __ballot(sat);
-    if (lane == 0 && mask)
-      atomicAdd(reinterpret_cast<unsigned long long *>(&st.ctrl->tile_recomputes),
-                (unsigned long long)__popcll(mask));
-    while (mask) {
-      const int src = __ffsll((long long)mask) - 1;
-      mask &= mask - 1;
-      const int vt = t0 + src;
-      if (st.dtype == 1) recompute_tile_bf16<KB>(st, row, vt, lane, all);
-      else recompute_tile_f32<KB>(st, row, vt, lane, all);
-    }
-  }
-  mine = 0ull;
+    if (found == 0) return lse;
+    // The wave's own writes, read by its other lanes.
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    cand_key last = ~0ull;
 #pragma unroll 1
-  for (int r = 0; r < k; ++r) {
-    const cand_key best = group_max_key<G>(all.k[0]);
-    if (lane == r) mine = best;
-    if (all.k[0] == best) {
-#pragma unroll
-      for (int j = 0; j + 1 < KB; ++j) all.k[j] = all.k[j + 1];
-      all.k[KB - 1] = 0ull;
+    for (int r = 0; r < k; ++r) {
+      cand_key best = own < last ? own : 0ull;
+#pragma unroll 1
+      for (int i = lane; i < found * 128; i += 64) best = sat_keys[i] < last && sat_keys[i] > best ? sat_keys[i] : best;
+      last = group_max_key<64>(best);
+      if (lane == r) mine = last;
     }
+    return lse;
   }
-  return lse;
 }
 
 // Row merge as its own kernel (wave per row), for the single-expansion
 // debug entry point: writes lse and the k best log-probabilities/tokens.
 template <int KB, int TK>
-__global__ __launch_bounds__(256) void k_rowmerge(DevState st) {
+__global__ __launch_bounds__(256, 4) void k_rowmerge(DevState st) {
   const int R = st.ctrl->R;
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= R) return;
   cand_key mine;
   const int k = st.k;
-  const double lse = merge_row<KB, TK, 64>(st, row, lane, k, mine);
+  __shared__ cand_key sat_keys[TK < KB ? 4 : 1][TK < KB ? SAT_MAX * 128 : 1];
+  const double lse = merge_row<KB, TK, 64>(st, row, lane, k, sat_keys[TK < KB ? threadIdx.x >> 6 : 0], mine);
   if (lane == 0) st.r_lse[row] = lse;
   if (lane < k) {
     st.top_lp[(size_t)row * k + lane] = (double)key_val(mine) - lse;
@@ -369,7 +379,7 @@ struct Cand {
 };
 
 template <int KB, int TK, int NT>
-__global__ __launch_bounds__(NT) void k_beam(DevState st) {
+__global__ __launch_bounds__(NT, 1) void k_beam(DevState st) {
   constexpr int G = NT == BEAM_THREADS_WAVE ? 8 : 64;                       // lanes per parent row
   constexpr int T1 = NT > 64 ? 64 : 0, T2 = NT > 128 ? 128 : 0;             // threads with work of their own
   const int b = blockIdx.x;
@@ -411,6 +421,8 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
   __shared__ int npar[KMAX_SUPPORTED], ntok[KMAX_SUPPORTED], nstat[KMAX_SUPPORTED];
   __shared__ int opar[KMAX_SUPPORTED], otok[KMAX_SUPPORTED], ostat[KMAX_SUPPORTED];
   __shared__ int nw_sh, nact_sh, no_sh;
+  // Recomputed keys of a row merge's rare case, per wave.
+  __shared__ cand_key sat_keys[TK < KB ? NT / 64 : 1][TK < KB ? SAT_MAX * 128 : 1];
   // Candidates (at most k KC list entries + k no-ops) and the ranks kept.
   __shared__ Cand cand[KMAX_SUPPORTED * (KMAX_SUPPORTED + 1)];
   __shared__ double r_score[2 * KMAX_SUPPORTED];
@@ -435,7 +447,7 @@ __global__ __launch_bounds__(NT) void k_beam(DevState st) {
     if (sl_status[par] != SLOT_ACTIVE) continue;
     const int gl = lane % G;
     cand_key mine;
-    const double lse = merge_row<KB, TK, G>(st, sl_row[par], gl, KC, mine);
+    const double lse = merge_row<KB, TK, G>(st, sl_row[par], gl, KC, sat_keys[TK < KB ? wave : 0], mine);
     if (gl < KC) {
       ch_lp[par * KC + gl] = (double)key_val(mine) - lse;
       ch_tok[par * KC + gl] = key_idx(mine);
@@ -851,8 +863,13 @@ hipError_t launch_beam(const DevState &st, hipStream_t s) {
         break;                                                                     \
       }                                                                            \
     }                                                                              \
-    if (small) SB_BEAM_NT(KB, TK, BEAM_THREADS_SMALL);                             \
-    else SB_BEAM_NT(KB, TK, BEAM_THREADS);                                         \
+    if constexpr (TK == KB) {                                                      \
+      if (small) {                                                                 \
+        SB_BEAM_NT(KB, TK, BEAM_THREADS_SMALL);                                    \
+        break;                                                                     \
+      }                                                                            \
+    }                                                                              \
+    SB_BEAM_NT(KB, TK, BEAM_THREADS);                                              \
   } while (0)
   switch (st.kbucket) {
     case 4: SB_BEAM(4, 4); break;
