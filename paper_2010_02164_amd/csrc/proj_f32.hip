@@ -124,7 +124,10 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
                         st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
   const SplitScale sc(st.w_scale + vt * TV + 32 * wv + 4 * (lane >> 5));
 #pragma unroll
-  for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
+  for (int b = 0; b < NB; ++b) {
+    tot[b] = sc.apply(tot[b]);
+    asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
+  }
   tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R);
 }
 

@@ -59,3 +59,12 @@ def test_beam_update_registers(kernels):
     assert len(beam) >= 10
     for name, (vgprs, spills) in beam.items():
         assert vgprs <= 128 and spills == 0, (name, vgprs, spills)
+
+
+def test_projection_registers(kernels):
+    """Two 4-wave workgroups per compute unit (256 registers a lane), nothing
+    spilled by the epilogue's longest key lists."""
+    proj = {k: v for k, v in kernels.items() if "k_proj" in k or "k_kv_append" in k}
+    assert len(proj) == 7
+    for name, (vgprs, spills) in proj.items():
+        assert vgprs <= 256 and spills == 0, (name, vgprs, spills)
