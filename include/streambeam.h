@@ -82,14 +82,18 @@ typedef enum {
 typedef enum { SB_RULE_PAPER = 0, SB_RULE_FAIRSEQ = 1 } sb_rule;
 
 /* Storage type of weights, h0 and decoder states. SB_F32: fp32 everywhere
- * (fp32 accumulation; the recurrence on the fp32 MFMA, the projection's
- * products from pairs of fp16 values that hold the 24 bits of each operand,
- * with an error against 64 bits below the fp32 MFMA's). SB_BF16: bf16 weights and states; the
- * projection accumulates in fp32; the recurrence pre-activation is the
- * exact sum of the bf16 products (integer digit products, d a multiple of
- * 256 up to 2048; otherwise, or when W_h has many values far below its
- * rows' largest, an fp64 sum), rounded once to fp64, so that the rounded
- * bf16 state is reproducible. h0 values must be finite. */
+ * (fp32 accumulation, the recurrence on the fp32 MFMA). The projection takes a
+ * product from pairs of fp16 values, each off by up to 2^-21 of itself; sums of
+ * many such products are rounded less often than on the fp32 MFMA (2-norm error
+ * against 64 bits with N(0, 1/d) weights and tanh states, d = 64 / 256 / 1024:
+ * 0.9 / 1.3 / 2.3e-7, the fp32 MFMA's 1.1 / 2.1 / 4.1e-7). A W_out row's values
+ * outside a range of 2^29 are added in fp32; where they are many, or a row has
+ * fewer than 32 + d/4 non-zero values, its 128 rows use the fp32 MFMA.
+ * SB_BF16: bf16 weights and states; the projection accumulates in fp32; the
+ * recurrence pre-activation is the exact sum of the bf16 products (integer
+ * digit products, d a multiple of 256 up to 2048; otherwise, or when W_h has
+ * many values far below its rows' largest, an fp64 sum), rounded once to fp64,
+ * so that the rounded bf16 state is reproducible. h0 values must be finite. */
 typedef enum { SB_F32 = 0, SB_BF16 = 1 } sb_dtype;
 
 /* Status of a finalized hypothesis. */

@@ -55,8 +55,8 @@ struct Layout {
   size_t ctrl, q_h0, q_Lx, q_ml, b_input, b_steps, b_row0, b_mask, b_Lx, b_par, b_ml, b_nout, b_order, s_status, s_score, s_tok, s_h,
       bp, r_slot, r_hsrc, r_y, r_t, r_Lx, r_lse, hbuf, part, top_lp, top_tok,
       o_count, o_hyp, o_tok, o_pack, o_off, wh_t, kvs, anc, wkv_t, xbuf, attn_part, wout_t, wd3, w_exp, w_ln, w_li,
-      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, hsplit, total;
-  size_t extra;   // bytes of the last regions: w_scale, hsplit, b_Lx
+      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, w_nfar, w_far, w_kinds, hsplit, total;
+  size_t extra;   // bytes of the last regions: b_Lx, and the fp32 projection's besides W_out
 };
 
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
@@ -158,6 +158,9 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
   L.b_Lx = take(n * 4);
   if (m.dtype == SB_F32) {
     L.w_scale = take(S * 128 * 4);
+    L.w_nfar = take(S * 4 * 4);
+    L.w_far = take(S * 4 * SPLIT_FAR * sizeof(FarValue));
+    L.w_kinds = take(4);
     L.hsplit = take((Rm + 31) / 32 * 32 * d * 4);
   }
   L.total = off;
@@ -341,7 +344,8 @@ sb_status launch_timed_step(sb_decoder *dec) {
 // their own behind it: a row's split state is as large as its fp32 state,
 // which the workspace holds twice (candidate and new state), so the split
 // states are at most half of the limit, plus a 32-row block's padding (of at
-// most 4096 values), 4 bytes per W_out row of at least 256 and 4 per beam.
+// most 4096 values) and 4 bytes per beam; 20 bytes per W_out row go with at
+// least 256 that are counted, so they are largest where the states are small.
 constexpr size_t SCRATCH_EXTRA_BYTES = SB_NOALLOC_SCRATCH_BYTES / 2 + (4u << 20);
 constexpr size_t SCRATCH_BYTES = SB_NOALLOC_SCRATCH_BYTES + SCRATCH_EXTRA_BYTES;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
@@ -484,6 +488,9 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
   st.wout_t = w + L.wout_t;
   if (model->dtype == SB_F32) {
     st.w_scale = reinterpret_cast<float *>(w + L.w_scale);
+    st.w_nfar = reinterpret_cast<int32_t *>(w + L.w_nfar);
+    st.w_far = reinterpret_cast<FarValue *>(w + L.w_far);
+    st.w_kinds = reinterpret_cast<int32_t *>(w + L.w_kinds);
     st.hsplit = w + L.hsplit;
   }
   st.wh_t = model->dtype == SB_F32 ? reinterpret_cast<const float4 *>(w + L.wh_t) : nullptr;
@@ -535,7 +542,7 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
     for (int i = 0; i < 2; ++i)
       if (hipEventCreateWithFlags(&dec->poll_ev[i], hipEventDisableTiming) != hipSuccess) return SB_E_HIP;
   }
-  if (launch_init(st, dec->stream) != hipSuccess) return SB_E_HIP;
+  if (launch_init(st, dec->stream, true) != hipSuccess) return SB_E_HIP;
   if (launch_relayout_wout(st, dec->stream) != hipSuccess) return SB_E_HIP;
   if (launch_relayout_wh(st, dec->stream) != hipSuccess) return SB_E_HIP;
   if (model->kv_layers > 0 &&

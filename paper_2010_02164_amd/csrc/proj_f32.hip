@@ -5,17 +5,24 @@
 //
 // The fp32 MFMA peaks at 157 TFLOP/s, the fp16 MFMA at 2.5 PFLOP/s, so each
 // operand is split into two fp16 values: x scaled by a power of two (a W_out
-// row so that its largest value is below 2^15, a state by 2^14) is
-// hi + lo / 2048 with hi = fp16(x) and lo = fp16(2048 (x - hi)). x - hi is
-// exact in fp32 and has at most 13 significant bits, so hi + lo / 2048 is x
-// to at most one unit in the last of its 24 bits (exact for three values in
-// four), for every value down to 2^-27 of the row's scale. Then
-//   w h = hi hi' + (hi lo' + lo hi') / 2048 + (lo lo' <= 2^-24 |w h|, dropped)
+// row so that its window, below, ends at 2^15, a state by 2^14) is
+// hi + lo / 4096 with hi = fp16(x) and lo = fp16(4096 (x - hi)), and
+//   w h = hi hi' + (hi lo' + lo hi') / 4096 + (lo lo', up to 2^-22 |w h|: dropped)
 // is three fp16 MFMAs accumulated in fp32. Over 64 values of K the cross
 // terms are summed apart, scaled once and added to the running sum, so that
 // they meet its rounding once. Error against 64 bits (relative 2-norm,
-// N(0, 1/d) weights, tanh states) at d = 64 / 256 / 1024: 0.9 / 1.2 / 2.3e-7,
+// N(0, 1/d) weights, tanh states) at d = 64 / 256 / 1024: 0.9 / 1.3 / 2.3e-7,
 // the fp32 MFMA's two half sums: 1.1 / 2.1 / 4.1e-7.
+//
+// That holds for sums of many products of values within the pairs' range;
+// W_out rows of another kind are found when they are split (k_split_wout):
+//  - A row's window is the 29 octaves that hold most of its values. The others
+//    (a large negative weight that masks a token while a unit is on, an
+//    infinite one, a value next to zero) are far values: zero in the pairs,
+//    listed per 32-row slice and added in fp32 to the finished sums.
+//  - A tile with more far values than a slice's list holds, or with a row of
+//    fewer than 32 + d / 4 non-zero values, where the fp32 MFMA's error is the
+//    smaller one (split_min_terms), takes its products on the fp32 MFMA.
 //
 // Bound: at d = 1024, |V| = 32000 a step of up to 64 rows by streaming W_out
 // (131 MB at 5.4 TB/s: 24.4 us, was 31.0), larger ones by the fp16 MFMA at
@@ -109,25 +116,105 @@ __device__ __forceinline__ void split_mainloop(unsigned char (*stage)[NBM * SPLI
   }
 }
 
+// The same tile on the fp32 MFMA, from W_out and the states themselves: each K
+// half in chunks of 32 values, piece q and element e of a chunk feeding k and
+// k + 16, then the halves added, the sums the recompute of a saturated tile
+// repeats (beam.hip). The states pass through the same LDS buffers, in
+// fragments [4 pieces][64 lanes][4 floats]. Single steps with every tile here,
+// d = 1024, |V| = 32000: 193 / 640 rows 197 / 421 us (110 / 202 on pairs; 250 /
+// 490 with the projection on the fp32 MFMA throughout, in 8-wave workgroups).
+template <int NB>
+__device__ __forceinline__ void fp32_mainloop(unsigned char (*stage)[NBM * SPLIT_CHUNK], const float *wl,
+                                              const float *sl, const uint32_t *row, int d, f16v *tot) {
+  constexpr int KC = 32, BLOCK = 32 * KC * 4;
+  const int tid = threadIdx.x, lane16 = (tid & 63) * 16, nch = d / KC;
+  f4 a[4], sg[NB];
+  f16v first[NB];
+  auto loadA = [&](int c) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = *reinterpret_cast<const f4 *>(wl + c * KC + 4 * q);
+  };
+  auto loadS = [&](int c) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) sg[b] = *reinterpret_cast<const f4 *>(sl + c * KC + row[b]);
+  };
+  auto storeS = [&](unsigned char *buf) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) *reinterpret_cast<f4 *>(buf + b * BLOCK + tid * 16) = sg[b];
+  };
+  loadS(0);
+  loadA(0);
+  storeS(stage[0]);
+  loadS(min(1, nch - 1));
+  __syncthreads();
+#pragma unroll 1
+  for (int c = 0; c < nch; ++c) {
+    if (c == nch / 2) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        first[b] = tot[b];
+        tot[b] = f16v{};
+      }
+    }
+    if (c + 1 < nch) storeS(stage[(c + 1) & 1]);
+    loadS(min(c + 2, nch - 1));
+    const unsigned char *buf = stage[c & 1] + lane16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const f4 x = *reinterpret_cast<const f4 *>(buf + b * BLOCK + q * FRAG);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tot[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][e], x[e], tot[b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    loadA(min(c + 1, nch - 1));
+    __syncthreads();
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tot[b][r] = first[b][r] + tot[b][r];
+}
+
+// What k_split_wout found in W_out besides plain rows (bits of *w_kinds).
+constexpr int KIND_FAR = 1, KIND_FP32 = 2;
+
 // Tile: vocabulary tile vt x NB blocks of 32 rows from row r0.
-template <int KB, int NB>
+template <int KB, bool PLAIN, int NB>
 __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm, int vt, int r0, int R) {
   constexpr int D = NB >= 4 ? 2 : NB == 3 ? 3 : 4;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nch = st.d / SPLIT_K;
-  const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
+  const int slice = vt * 4 + wv;
   f16v tot[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) tot[b] = f16v{};
-  split_mainloop<NB, D>(sm.stage, st.wout_t + ((size_t)(vt * 4 + wv) * nch) * SPLIT_CHUNK + lane * 16,
-                        st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
-  const SplitScale sc(st.w_scale + vt * TV + 32 * wv + 4 * (lane >> 5));
+  const float *states = static_cast<const float *>(st.proj_in);   // under 4 GiB
+  auto row_at = [&](int b) { return (uint32_t)min(r0 + 32 * b + (lane & 31), R - 1) * (uint32_t)st.d; };
+  if (!PLAIN && split_tile_fp32(st, vt)) {
+    const float *w = static_cast<const float *>(st.W_out) + (size_t)min(32 * slice + (lane & 31), st.V - 1) * st.d;
+    uint32_t row[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    tot[b] = sc.apply(tot[b]);
-    asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
+    for (int b = 0; b < NB; ++b) row[b] = row_at(b) + 16 * h;
+    fp32_mainloop<NB>(sm.stage, w + 16 * h, states + 4 * wv, row, st.d, tot);
+  } else {
+    const int nch = st.d / SPLIT_K;
+    const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
+    split_mainloop<NB, D>(sm.stage, st.wout_t + (size_t)slice * nch * SPLIT_CHUNK + lane * 16,
+                          st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
+    const SplitScale sc(st.w_scale + 32 * slice + 4 * h);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
+    if (const int nfar = PLAIN ? 0 : st.w_nfar[slice]) {
+      const float *x[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) x[b] = states + row_at(b);
+      add_far<NB>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, h, x, tot);
+    }
   }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
   tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R);
 }
 
@@ -160,11 +247,10 @@ __device__ __forceinline__ int split_tile_blocks(int R, int S, int n_cu) {
 // the row tiles of one vocabulary tile run side by side on one XCD and share
 // its L2 copy of the W_out tile; rounds alternate direction, so that a
 // workgroup which drew a full row tile draws a partial one in the next.
-template <int KB>
-__global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
-  const int R = st.ctrl->R;
-  if (R <= 0) return;
-  __shared__ SplitSmem<KB> sm;
+// A W_out of plain rows only (most are) has a walk of its own: a kind looked up
+// per tile, ahead of its K loop, cost 0.3 us per step.
+template <int KB, bool PLAIN>
+__device__ __forceinline__ void split_walk(const DevState &st, SplitSmem<KB> &sm, int R) {
   const int bt = split_tile_blocks(R, st.S, st.n_cu);
   const int nra = (R + 32 * bt - 1) / (32 * bt);
   const int T = st.S * nra;
@@ -179,51 +265,141 @@ __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
     order.at(tile, vt, rt);
     const int r0 = rt * bt * 32;
     switch (min(bt, (R - r0 + 31) >> 5)) {
-      case 1: split_tile<KB, 1>(st, sm, vt, r0, R); break;
-      case 2: split_tile<KB, 2>(st, sm, vt, r0, R); break;
-      case 3: split_tile<KB, 3>(st, sm, vt, r0, R); break;
-      default: split_tile<KB, 4>(st, sm, vt, r0, R); break;
+      case 1: split_tile<KB, PLAIN, 1>(st, sm, vt, r0, R); break;
+      case 2: split_tile<KB, PLAIN, 2>(st, sm, vt, r0, R); break;
+      case 3: split_tile<KB, PLAIN, 3>(st, sm, vt, r0, R); break;
+      default: split_tile<KB, PLAIN, 4>(st, sm, vt, r0, R); break;
     }
   }
 }
 
-// W_out, once per decoder (one workgroup per 32 vocabulary rows): the scale
-// of every row, then its split values in fragment order. With every |w| of
-// the row below 2^e, values are multiplied by 2^(15 - e) and a sum of
-// products with 2^14-scaled states by 2^(e - 29); e is held to [-90, 128], so
-// that both factors are normal numbers. Layout: [S][4 slices][d / 64 chunks]
-// [4 steps][hi, lo][64 lanes][8 fp16], lane (h, l) of step s holding
-// k = 64 chunk + 16 s + 8 h .. + 7 of vocabulary row 128 vt + 32 slice + l
-// (zero past V). An infinite value is a low part alone: it then meets only the
-// state's high part (which is not zero for |h| above 2^-39), where the high
-// part's product with a state's low part of zero would be NaN.
+template <int KB>
+__global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
+  const int R = st.ctrl->R, kinds = *st.w_kinds;
+  if (R <= 0 || kinds < 0) return;   // kinds is 0 or above: tested here so that both loads are one wait
+  __shared__ SplitSmem<KB> sm;
+  if (kinds == 0) split_walk<KB, true>(st, sm, R);
+  else split_walk<KB, false>(st, sm, R);
+}
+
+// W_out, once per decoder (one workgroup per 32 vocabulary rows): the window
+// and scale of every row, then its split values in fragment order. A row's
+// window are the values whose exponent field is in [top - 28, top]: it ends at
+// the largest value where that leaves none below it, else lies where it holds
+// most (top is held to [36, 254], so that the factors below are normal
+// numbers). With e = top - 126, values are multiplied by 2^(15 - e) and a sum
+// of products with 2^14-scaled states by 2^(e - 29). Layout: [S][4 slices]
+// [d / 64 chunks][4 steps][hi, lo][64 lanes][8 fp16], lane (h, l) of step s
+// holding k = 64 chunk + 16 s + 8 h .. + 7 of vocabulary row
+// 128 vt + 32 slice + l (zero past V, and for far values).
+__device__ __forceinline__ int exp_field(float x) { return (int)((__float_as_uint(x) >> 23) & 0xFFu); }
+__device__ __forceinline__ bool is_far(float x, int top) {
+  const int e = exp_field(x);
+  return x != 0.0f && (e > top || e <= top - SPLIT_OCTAVES);   // NaN and infinities: e = 255
+}
+
 __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
-  __shared__ float up[32];
-  const int d = st.d, nst = d / 16, tid = threadIdx.x;
-  const int vb = blockIdx.x * 32;
+  __shared__ int tops[32];
+  __shared__ uint32_t hist[32][128];   // two 16-bit counts per word: values of a row by exponent field
+  __shared__ int wave_far[4];
+  const int d = st.d, nst = d / 16, tid = threadIdx.x, lane = tid & 63;
+  const int vb = blockIdx.x * 32, row = tid >> 3, part = tid & 7;
   const float *W = static_cast<const float *>(st.W_out);
-  {
-    const int v = vb + (tid >> 3);
-    float mx = 0.0f;
-    if (v < st.V)
-      for (int i = (tid & 7) * 4; i < d; i += 32) {
-        const f4 w = *reinterpret_cast<const f4 *>(W + (size_t)v * d + i);
+  const float *wr = W + (size_t)min(vb + row, st.V - 1) * d;   // the thread's share: 4 values of every 32
+  const bool real = vb + row < st.V;
+  uint32_t most_bits = 0u, least = 0xFFFFFFFFu;   // largest magnitude; smallest not zero, less one
+  int terms = 0;
+  if (real)
+    for (int i = part * 4; i < d; i += 32) {
+      const u4 w = *reinterpret_cast<const u4 *>(wr + i);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(w[q]));
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t u = w[q] & 0x7FFFFFFFu;
+        most_bits = max(most_bits, u);
+        least = min(least, u - 1u);
+        terms += u != 0u;
       }
+    }
 #pragma unroll
-    for (int o = 4; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    int e = 0;
-    if (mx >= INFINITY) e = 128;
-    else if (mx > 0.0f) frexpf(mx, &e);
-    e = min(max(e, -90), 128);
-    if ((tid & 7) == 0) {
-      up[tid >> 3] = ldexpf(1.0f, 15 - e);
-      st.w_scale[v] = ldexpf(1.0f, e - 29);
+  for (int o = 4; o > 0; o >>= 1) {
+    most_bits = max(most_bits, (uint32_t)__shfl_xor((int)most_bits, o, 64));
+    least = min(least, (uint32_t)__shfl_xor((int)least, o, 64));
+    terms += __shfl_xor(terms, o, 64);
+  }
+  const int largest = (int)(most_bits >> 23), smallest = terms ? (int)((least + 1u) >> 23) : 255;
+  int top = min(max(largest, 36), 254);
+  const bool wide = largest == 255 || smallest <= top - SPLIT_OCTAVES;
+  bool few = terms > 0 && terms < split_min_terms(d);
+  int nfar = 0;
+  const bool any_wide = __syncthreads_or(wide);
+  if (any_wide) {
+    for (int i = tid; i < 32 * 128; i += 256) (&hist[0][0])[i] = 0u;
+    __syncthreads();
+    if (wide)
+      for (int i = part * 4; i < d; i += 32) {
+        const f4 w = *reinterpret_cast<const f4 *>(wr + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (w[q] != 0.0f) atomicAdd(&hist[row][exp_field(w[q]) >> 1], exp_field(w[q]) & 1 ? 65536u : 1u);
+      }
+    __syncthreads();
+    if (wide) {
+      auto count = [&](int e) { return e < 0 ? 0 : (int)((hist[row][e >> 1] >> (16 * (e & 1))) & 0xFFFFu); };
+      int held = 0;
+      for (int e = top; e > top - SPLIT_OCTAVES; --e) held += count(e);
+      int most = held;
+      for (int t = top - 1; t >= max(36, smallest); --t) {   // of equal ones the lowest: it ends at its largest value
+        held += count(t + 1 - SPLIT_OCTAVES) - count(t + 1);
+        if (held >= most) {
+          most = held;
+          top = t;
+        }
+      }
+      few = most > 0 && most < split_min_terms(d);
+    }
+    // Places of the far values: by row, then by share.
+    int n = 0;
+    if (wide)
+      for (int i = part * 4; i < d; i += 32) {
+        const f4 w = *reinterpret_cast<const f4 *>(wr + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += is_far(w[q], top);
+      }
+    int at = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(at, o, 64);
+      if (lane >= o) at += y;
+    }
+    if (lane == 63) wave_far[tid >> 6] = at;
+    at -= n;
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      at += x < tid >> 6 ? wave_far[x] : 0;
+      nfar += wave_far[x];
+    }
+    if (n > 0 && nfar <= SPLIT_FAR) {
+      FarValue *f = st.w_far + (size_t)blockIdx.x * SPLIT_FAR + at;
+      for (int i = part * 4; i < d; i += 32) {
+        const f4 w = *reinterpret_cast<const f4 *>(wr + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (is_far(w[q], top)) *f++ = FarValue{row << 16 | (i + q), w[q]};
+      }
     }
   }
-  __syncthreads();
-  const int ln = tid & 63, v = vb + (ln & 31);
+  if (part == 0) {
+    tops[row] = top;
+    st.w_scale[vb + row] = ldexpf(1.0f, top - 126 - 29);
+  }
+  const bool fp32 = __syncthreads_or(few) || nfar > SPLIT_FAR;
+  if (tid == 0) {
+    st.w_nfar[blockIdx.x] = fp32 ? -1 : nfar;
+    if (fp32 || nfar > 0) atomicOr(st.w_kinds, fp32 ? KIND_FP32 : KIND_FAR);
+  }
+  const int v = vb + (lane & 31), vtop = tops[lane & 31];
+  const float up = ldexpf(1.0f, 15 + 126 - vtop);
   for (int s = tid >> 6; s < nst; s += 4) {
     union {
       _Float16 f[8];
@@ -232,18 +408,17 @@ __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
     hi.u = u4{0u, 0u, 0u, 0u};
     lo.u = hi.u;
     if (v < st.V) {
-      const float *src = W + (size_t)v * d + 16 * s + 8 * (ln >> 5);
+      const float *src = W + (size_t)v * d + 16 * s + 8 * (lane >> 5);
+      float x[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float x = src[i] * up[ln & 31];
-        split_f16(x, hi.f[i], lo.f[i]);
-        if (fabsf(x) == INFINITY) {
-          hi.f[i] = (_Float16)0.0f;
-          lo.f[i] = (_Float16)x;
-        }
-      }
+      for (int i = 0; i < 8; ++i) x[i] = src[i];
+      if (any_wide)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = is_far(x[i], vtop) ? 0.0f : x[i];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) split_f16(x[i] * up, hi.f[i], lo.f[i]);
     }
-    unsigned char *dst = st.wout_t + ((size_t)blockIdx.x * nst + s) * (2 * FRAG) + ln * 16;
+    unsigned char *dst = st.wout_t + ((size_t)blockIdx.x * nst + s) * (2 * FRAG) + lane * 16;
     *reinterpret_cast<u4 *>(dst) = hi.u;
     *reinterpret_cast<u4 *>(dst + FRAG) = lo.u;
   }

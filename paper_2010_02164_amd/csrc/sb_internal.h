@@ -26,6 +26,14 @@ struct RowAux {
 };
 static_assert(sizeof(RowAux) == 128, "RowAux is copied as 8 x 16 bytes");
 
+// A W_out value outside its row's window (fp32 projection): column and, above
+// bit 16, the row within its 32-row vocabulary slice.
+constexpr int SPLIT_FAR = 64;   // listed per slice
+struct FarValue {
+  int32_t at;
+  float val;
+};
+
 // Device-side control block: the scheduler state of Alg. 1 and the counters.
 struct DevCtrl {
   int32_t n_queued;   // inputs submitted so far
@@ -130,6 +138,9 @@ struct DevState {
   // fp32 split into fp16 pairs (k_split_wout) with the scale of every row.
   unsigned char *wout_t;
   float *w_scale;          // fp32: [S * 128]
+  int32_t *w_nfar;         // fp32: [S * 4] far values of a 32-row slice, -1: the slice needs the fp32 MFMA
+  FarValue *w_far;         // fp32: [S * 4][SPLIT_FAR]
+  int32_t *w_kinds;        // fp32: 0, or what W_out holds besides plain rows (proj_f32.hip)
   unsigned char *hsplit;   // fp32: the step's new states split (split_state_off)
   // sizes and parameters
   int32_t n, k, d, V, M, max_len_cap, refill_thr, S, R_max, dtype, kv_layers, max_inputs;
@@ -179,7 +190,7 @@ hipError_t launch_kv_append(const DevState &st, hipStream_t s);
 hipError_t launch_attn(const DevState &st, hipStream_t s);
 hipError_t launch_backtrack(const DevState &st, int q0, int q1, hipStream_t s);
 hipError_t launch_pack(const DevState &st, int q0, int q1, hipStream_t s);
-hipError_t launch_init(const DevState &st, hipStream_t s);
+hipError_t launch_init(const DevState &st, hipStream_t s, bool create = false);
 hipError_t launch_split_wout(const DevState &st, hipStream_t s);
 hipError_t launch_proj_split(const DevState &st, hipStream_t s);
 hipError_t launch_relayout_wout(const DevState &st, hipStream_t s);

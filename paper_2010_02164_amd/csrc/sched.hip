@@ -421,7 +421,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
 }
 
 // Reset of every beam, slot, output count and the control block.
-__global__ void k_init(DevState st) {
+__global__ void k_init(DevState st, bool create) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < st.n) {
     st.b_input[i] = -1;
@@ -435,6 +435,7 @@ __global__ void k_init(DevState st) {
     st.s_status[i] = SLOT_EMPTY;
   }
   if (i < st.max_inputs) st.o_count[i] = 0;
+  if (i == 0 && create && st.w_kinds) *st.w_kinds = 0;   // set by the split of W_out that follows
   if (i == 0) {
     DevCtrl z = {};
     z.done = 1;
@@ -456,10 +457,10 @@ hipError_t launch_sched(const DevState &st, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_init(const DevState &st, hipStream_t s) {
+hipError_t launch_init(const DevState &st, hipStream_t s, bool create) {
   int m = st.n * st.k;
   if (st.max_inputs > m) m = st.max_inputs;
-  hipLaunchKernelGGL(k_init, dim3((m + 255) / 256), dim3(256), 0, s, st);
+  hipLaunchKernelGGL(k_init, dim3((m + 255) / 256), dim3(256), 0, s, st, create);
   return hipGetLastError();
 }
 

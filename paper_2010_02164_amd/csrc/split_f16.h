@@ -11,12 +11,23 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 constexpr int SPLIT_K = 64;                        // K values per chunk
 constexpr int SPLIT_CHUNK = SPLIT_K / 16 * 2048;   // bytes of a 32-row block's chunk: [4 steps][hi, lo][64 lanes][16 B]
 constexpr float SPLIT_H_SCALE = 16384.0f;          // states are split after scaling by 2^14 (|h| <= 1)
+constexpr float SPLIT_LO = 4096.0f;                // scale of the low parts
 
-// x = hi + lo / 2048, to one unit in the last of x's 24 bits or better.
+// x = hi + lo / 4096. x - hi has at most 13 significant bits, so the pair is x
+// to one unit in the last of its 24 bits (exact for three values in four) for
+// 2^-14 <= |x| <= 2^15; below that range it loses bits.
+constexpr int SPLIT_OCTAVES = 29;
 __device__ __forceinline__ void split_f16(float x, _Float16 &hi, _Float16 &lo) {
   hi = (_Float16)x;
-  lo = (_Float16)((x - (float)hi) * 2048.0f);
+  lo = (_Float16)((x - (float)hi) * SPLIT_LO);
 }
+
+// A product of pairs is off by up to 2^-21.2 of itself (the dropped lo lo' and
+// the pairs' last unit), against 2^-24 on the fp32 MFMA; a sum of many products
+// is off by less than there, because its running value is rounded less often.
+// The two meet (2-norm against 64 bits, N(0, 1) weights, tanh states) at about
+// 46 / 98 / 290 non-zero products for d = 64 / 256 / 1024.
+__host__ __device__ constexpr int split_min_terms(int d) { return 32 + d / 4; }
 
 // Byte offset of value k of row r in the split states [R / 32][d / 16][hi, lo]
 // [64 lanes][8 fp16]; the lo part follows 1024 bytes later.
@@ -33,7 +44,7 @@ __device__ __forceinline__ void split_step(u4 wh, u4 wl, u4 bh, u4 bl, f16v &tot
 }
 __device__ __forceinline__ void split_flush(const f16v &c, f16v &tot) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) tot[r] = fmaf(c[r], 1.0f / 2048.0f, tot[r]);
+  for (int r = 0; r < 16; ++r) tot[r] = fmaf(c[r], 1.0f / SPLIT_LO, tot[r]);
 }
 
 // tot += W chunk (8 fragments af: hi, lo of 4 steps) x state chunk (fragments
@@ -43,6 +54,12 @@ __device__ __forceinline__ void split_chunk(const u4 *af, const u4 *bs, int bstr
 #pragma unroll
   for (int s = 0; s < 4; ++s) split_step(af[2 * s], af[2 * s + 1], bs[2 * s * bstride], bs[(2 * s + 1) * bstride], tot, c);
   split_flush(c, tot);
+}
+
+// Whether a vocabulary tile's products are taken on the fp32 MFMA.
+__device__ __forceinline__ bool split_tile_fp32(const DevState &st, int vt) {
+  const int4 n = *reinterpret_cast<const int4 *>(st.w_nfar + 4 * vt);
+  return (n.x | n.y | n.z | n.w) < 0;
 }
 
 // The 16 vocabulary rows' scales of a lane (register r: row 8 (r / 4) + r % 4
@@ -60,5 +77,42 @@ struct SplitScale {
     return z;
   }
 };
+
+// z[b] += the far values of a 32-row vocabulary slice (entries f[0..n)) times
+// row b's state, one fused product each in list order. The caller's lane half h
+// holds vocabulary rows 8 (r / 4) + 4 h + r % 4 of the slice in registers r.
+// The states of four entries are loaded at a time (past the end the last
+// entry's).
+template <int NB>
+__device__ __forceinline__ void add_far(const FarValue *f, int n, int h, const float *const *x, f16v *z) {
+  constexpr int U = 4;
+#pragma unroll 1
+  for (int i0 = 0; i0 < n; i0 += U) {
+    int at[U];
+    float w[U], hv[U][NB];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const FarValue e = f[min(i0 + u, n - 1)];
+      at[u] = __builtin_amdgcn_readfirstlane(e.at);
+      w[u] = e.val;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) hv[u][b] = x[b][at[u] & 0xFFFF];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u >= n) break;
+      const int row = at[u] >> 16, reg = 4 * (row >> 3) + (row & 3);
+      const bool mine = ((row >> 2) & 1) == h;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (r == reg) {
+#pragma unroll
+          for (int b = 0; b < NB; ++b) z[b][r] = mine ? fmaf(w[u], hv[u][b], z[b][r]) : z[b][r];
+        }
+    }
+  }
+}
 
 }  // namespace sb

@@ -297,3 +297,93 @@ def test_expand_one_lane_holds_the_best(gpu, cfg_i, k, per_tile):
     print(f"[expand] one lane {wl.cfg.dtype} k={k}", flush=True)
     assert len(set(tok[0].tolist()) & set(toks)) >= min(k, len(toks)) - 1
     _check_rows(wl, h_gpu, lp, tok, h_ref, lp_ref, lse)
+
+
+# Logits of chosen tokens to their last bits. All tokens but 16 are held 50
+# below, by a unit that is on (h = 1) in every row, and the first of the 16 has
+# a row of zeros: its logit is 0, and the returned log-probabilities' differences
+# to its own are the logits of the other 15. They are compared with 64-bit
+# products of W_out and the states the step returned, as a multiple of 2^-24 of
+# the products' sum of magnitudes.
+ON, OFF, FAINT = 3, 7, 11   # units that are 1, 0 and 1e-20 in every row
+
+
+def _logit_case(V, d, R, make, one_tile, seed=91):
+    """(logits [R, 15], 64-bit logits, sums of magnitudes): the 15 chosen rows
+    are make(rng, dense rows [15, d]); all in one 128-token tile or spread."""
+    rng = np.random.default_rng(seed)
+    wl = make_workload(scaled(1, N=4, V=V, d=d, k=16, M=16, n=-(-R // 16)))
+    E, Wh, W = wl.E.copy(), wl.W_h.copy(), wl.W_out.copy()
+    for u, e in ((ON, 40.0), (OFF, 0.0), (FAINT, 1e-20)):
+        Wh[u], E[:, u] = 0.0, e
+    W[:, ON] = -50.0
+    at = 128 * (V // 256) + 5 + (7 * np.arange(16) if one_tile else 0)
+    toks = at if one_tile else (5 + (V // 16) * np.arange(16))
+    rows = rng.standard_normal((15, d)) * d**-0.5
+    rows[:, [ON, OFF, FAINT]] = 0.0
+    W[toks[0]] = 0.0
+    W[toks[1:]] = make(rng, rows).astype(np.float32)
+    wl = dataclasses.replace(wl, E=E, W_h=Wh, W_out=W.astype(np.float32))
+    _, _, _, _, h, _, lp, tok, _, _ = _expand_case(wl, R, seed)
+    order = np.argsort(tok, axis=1)
+    assert np.array_equal(np.take_along_axis(tok, order, 1), np.tile(np.sort(toks), (R, 1)))
+    lp = np.take_along_axis(lp, order, 1)[:, np.argsort(np.argsort(toks))]
+    z = lp[:, 1:] - lp[:, :1]
+    w, h = wl.W_out[toks[1:]].astype(np.float64), h.astype(np.float64)
+    return z, h @ w.T, np.abs(h) @ np.abs(w).T
+
+
+def _set(cols, value):
+    def make(rng, rows):
+        rows[:, cols] = value if np.ndim(value) == 0 else np.asarray(value)[:, None]
+        return rows
+    return make
+
+
+def _keep(n):
+    def make(rng, rows):   # n non-zero values in a row
+        out = np.zeros_like(rows)
+        for r in range(15):
+            c = rng.choice(np.arange(12, rows.shape[1]), n, replace=False)
+            out[r, c] = rows[r, c]
+        return out
+    return make
+
+
+def _octaves(lo, hi, some=None):
+    def make(rng, rows):   # all values, or some of each row, over many powers of two
+        f = 2.0 ** rng.uniform(lo, hi, rows.shape)
+        for r in range(15 if some else 0):
+            f[r, rng.permutation(rows.shape[1])[some:]] = 1.0
+        return rows * f
+    return make
+
+
+# Units of 2^-24: a sum of n products rounded once per product is off by at most
+# n; of many products by about 2.2 at most over these samples on the fp32 MFMA,
+# and by up to 3.8 from pairs of fp16 (2^-21.2 = 7 for a single product).
+WIDE_ROWS = [
+    ("plain", lambda rng, rows: rows, 6), ("scaled", lambda rng, rows: rows * 2.0 ** rng.integers(-15, 1, (15, 1)), 6),
+    ("mask_1e9", _set([OFF], -1e9), 6), ("mask_1e12", _set([OFF], -1e12), 6), ("mask_3e38", _set([OFF], -3e38), 6),
+    ("two_masks_up", _set([OFF, FAINT], [1e21 * 2.0**-i for i in range(15)]), 6), ("faint", _set([FAINT], -1e21), 6),
+    ("tiny_values", _octaves(-50, -40, 3), 6), ("octaves", _octaves(-90, 0), 6), ("subnormal", _octaves(-140, -135, 80), 6),
+    ("one_term", _keep(1), 1), ("two_terms", _keep(2), 2), ("forty_terms", _keep(40), 6),
+]
+
+
+@pytest.mark.parametrize("V,d", [(1000, 64), (8320, 256), (8320, 1024)])
+@pytest.mark.parametrize("name,make,units", WIDE_ROWS, ids=[c[0] for c in WIDE_ROWS])
+def test_expand_f32_wide_rows(gpu, name, make, units, V, d):
+    """W_out rows whose values span more than the fp16 pairs hold (a large finite
+    mask on a unit that is off, values next to zero), or with few non-zero ones,
+    give their logits as the fp32 MFMA did; the row merge's recomputation of a
+    saturated tile gives the same bits as the projection."""
+    got = []
+    for one_tile in (False, True):
+        z, ref, mag = _logit_case(V, d, 45, make, one_tile)
+        err = np.abs(z - ref) / mag * 2.0**24
+        print(f"[expand] f32 {name} V={V} d={d} one_tile={one_tile}: {err.max():.2f} units", flush=True)
+        # lp are doubles of up to 200: differences carry 2^-45 of their own
+        assert np.all(np.abs(z - ref) <= units * 2.0**-24 * mag + 2.0**-44)
+        got.append(z)
+    assert np.abs(got[0] - got[1]).max() <= 2.0**-44
