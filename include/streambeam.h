@@ -88,7 +88,8 @@ typedef enum { SB_RULE_PAPER = 0, SB_RULE_FAIRSEQ = 1 } sb_rule;
  * against 64 bits with N(0, 1/d) weights and tanh states, d = 64 / 256 / 1024:
  * 0.9 / 1.3 / 2.3e-7, the fp32 MFMA's 1.1 / 2.1 / 4.1e-7). A W_out row's values
  * outside a range of 2^29 are added in fp32; where they are many, or a row has
- * fewer than 32 + d/4 non-zero values, its 128 rows use the fp32 MFMA.
+ * fewer than 32 + d/4 non-zero values, its 128 rows use the fp32 MFMA, and so
+ * does a batch row with a state below 2^-29 or with as few that are not zero.
  * SB_BF16: bf16 weights and states; the projection accumulates in fp32; the
  * recurrence pre-activation is the exact sum of the bf16 products (integer
  * digit products, d a multiple of 256 up to 2048; otherwise, or when W_h has

@@ -55,7 +55,7 @@ struct Layout {
   size_t ctrl, q_h0, q_Lx, q_ml, b_input, b_steps, b_row0, b_mask, b_Lx, b_par, b_ml, b_nout, b_order, s_status, s_score, s_tok, s_h,
       bp, r_slot, r_hsrc, r_y, r_t, r_Lx, r_lse, hbuf, part, top_lp, top_tok,
       o_count, o_hyp, o_tok, o_pack, o_off, wh_t, kvs, anc, wkv_t, xbuf, attn_part, wout_t, wd3, w_exp, w_ln, w_li,
-      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, w_nfar, w_far, w_kinds, hsplit, total;
+      w_lv, wt_off, wt_col, wt_val, hd, s_hd, q_hd, haux, s_haux, q_haux, w_scale, w_nfar, w_far, hsplit, r_far, total;
   size_t extra;   // bytes of the last regions: b_Lx, and the fp32 projection's besides W_out
 };
 
@@ -160,8 +160,8 @@ Layout layout_of(const sb_model &m, const sb_params &p) {
     L.w_scale = take(S * 128 * 4);
     L.w_nfar = take(S * 4 * 4);
     L.w_far = take(S * 4 * SPLIT_FAR * sizeof(FarValue));
-    L.w_kinds = take(4);
     L.hsplit = take((Rm + 31) / 32 * 32 * d * 4);
+    L.r_far = take(Rm * 4);
   }
   L.total = off;
   L.extra = off - before;
@@ -247,9 +247,13 @@ __global__ void k_set_queued(DevCtrl *c, int32_t nq) {
 // pinned host memory) the tokens, positions and lengths come from there.
 __global__ __launch_bounds__(256) void k_debug_rows(DevState st, const int32_t *in, int32_t R) {
   const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r == 0) st.ctrl->R = R;
+  if (r == 0) {
+    st.ctrl->R = R;
+    st.ctrl->far = 0;
+  }
   if (r >= R) return;
   st.r_hsrc[r] = r;
+  if (st.r_far) st.r_far[r] = 0;
   if (in) {
     st.r_y[r] = in[r];
     st.r_t[r] = in[R + r];
@@ -344,7 +348,7 @@ sb_status launch_timed_step(sb_decoder *dec) {
 // their own behind it: a row's split state is as large as its fp32 state,
 // which the workspace holds twice (candidate and new state), so the split
 // states are at most half of the limit, plus a 32-row block's padding (of at
-// most 4096 values) and 4 bytes per beam; 20 bytes per W_out row go with at
+// most 4096 values), 4 bytes per beam and 4 per row; 20 bytes per W_out row go with at
 // least 256 that are counted, so they are largest where the states are small.
 constexpr size_t SCRATCH_EXTRA_BYTES = SB_NOALLOC_SCRATCH_BYTES / 2 + (4u << 20);
 constexpr size_t SCRATCH_BYTES = SB_NOALLOC_SCRATCH_BYTES + SCRATCH_EXTRA_BYTES;
@@ -490,8 +494,8 @@ sb_status init_decoder(sb_decoder *dec, const sb_model *model, const sb_params *
     st.w_scale = reinterpret_cast<float *>(w + L.w_scale);
     st.w_nfar = reinterpret_cast<int32_t *>(w + L.w_nfar);
     st.w_far = reinterpret_cast<FarValue *>(w + L.w_far);
-    st.w_kinds = reinterpret_cast<int32_t *>(w + L.w_kinds);
     st.hsplit = w + L.hsplit;
+    st.r_far = reinterpret_cast<int32_t *>(w + L.r_far);
   }
   st.wh_t = model->dtype == SB_F32 ? reinterpret_cast<const float4 *>(w + L.wh_t) : nullptr;
   st.wh16_t = model->dtype == SB_BF16 ? reinterpret_cast<const uint2 *>(w + L.wh_t) : nullptr;

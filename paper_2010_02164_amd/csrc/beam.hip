@@ -108,13 +108,13 @@ __device__ __forceinline__ f16v recompute_slice_f32(const DevState &st, int row,
   const int slice = vt * 4 + s, nfar = st.w_nfar[slice];
   f16v z = SplitScale(st.w_scale + 32 * slice + 4 * (lane >> 5)).apply(tot);
   if (nfar > 0) {
-    const float *h = static_cast<const float *>(st.proj_in) + (size_t)row * st.d;
-    add_far<1>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, lane >> 5, &h, &z);
+    const uint32_t at = (uint32_t)row * (uint32_t)st.d;
+    add_far<1>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, lane >> 5, static_cast<const float *>(st.proj_in), &at, &z);
   }
   return z;
 }
 
-// Logit z[v] of one row where the projection took the tile on the fp32 MFMA,
+// Logit z[v] of one row where the projection took it on the fp32 MFMA,
 // which adds its two products to the sum one after the other, lane half 0's
 // first: K halves in chunks of 32 values, per chunk the products of k and
 // k + 16, then the halves added.
@@ -169,7 +169,7 @@ __device__ __forceinline__ f16v recompute_slice_bf16(const DevState &st, int row
 __device__ __forceinline__ void recompute_tile(const DevState &st, int row, int vt, int lane, cand_key *keys) {
   const int h = lane >> 5, l32 = lane & 31;
   const float bias = st.beta * (float)(st.r_t[row] - st.r_Lx[row]);
-  if (st.dtype == 0 && split_tile_fp32(st, vt)) {
+  if (st.dtype == 0 && (split_tile_fp32(st, vt) || split_row_fp32(st, row))) {
 #pragma unroll 1
     for (int i = lane; i < 128; i += 64) {
       const int v = vt * 128 + i;

@@ -124,11 +124,11 @@ __device__ __forceinline__ void write_record(const DevState &st, int j, int vt, 
 
 // Epilogue of a tile of NB blocks (rows from r0) of vocabulary tile vt, by a
 // workgroup of 4 waves: wave wv's lane lists of its 32-token slice of each
-// block (logits z(b)), then one thread per row merges the four slices.
-// Ends with a barrier: LDS may be reused.
-template <int KB, int NB, class Z>
+// block (logits z(b)), then one thread per row merges the four slices, for
+// the rows that are `wanted`. Ends with a barrier: LDS may be reused.
+template <int KB, int NB, class Z, class Wanted>
 __device__ __forceinline__ void tile_epilogue(const DevState &st, float (*xch)[32 * TILE_BLOCKS][part_width(KB)],
-                                              Z &&z, int vt, int wv, int r0, int R) {
+                                              Z &&z, int vt, int wv, int r0, int R, Wanted &&wanted) {
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int v0 = vt * TV;
 #pragma unroll
@@ -146,7 +146,7 @@ __device__ __forceinline__ void tile_epilogue(const DevState &st, float (*xch)[3
     }
   }
   __syncthreads();
-  if (tid < 32 * NB && r0 + tid < R) {
+  if (tid < 32 * NB && r0 + tid < R && wanted(r0 + tid)) {
     const float *sl[4] = {xch[0][tid], xch[1][tid], xch[2][tid], xch[3][tid]};
     write_record<KB>(st, r0 + tid, vt, sl);
   }

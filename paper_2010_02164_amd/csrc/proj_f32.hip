@@ -5,7 +5,7 @@
 //
 // The fp32 MFMA peaks at 157 TFLOP/s, the fp16 MFMA at 2.5 PFLOP/s, so each
 // operand is split into two fp16 values: x scaled by a power of two (a W_out
-// row so that its window, below, ends at 2^15, a state by 2^14) is
+// row so that its window, below, ends at 2^15, as a state does) is
 // hi + lo / 4096 with hi = fp16(x) and lo = fp16(4096 (x - hi)), and
 //   w h = hi hi' + (hi lo' + lo hi') / 4096 + (lo lo', up to 2^-22 |w h|: dropped)
 // is three fp16 MFMAs accumulated in fp32. Over 64 values of K the cross
@@ -23,6 +23,10 @@
 //  - A tile with more far values than a slice's list holds, or with a row of
 //    fewer than 32 + d / 4 non-zero values, where the fp32 MFMA's error is the
 //    smaller one (split_min_terms), takes its products on the fp32 MFMA.
+// The recurrence counts the states of a row that are zero, and those below 2^-29,
+// which the pairs do not hold; a row with one of these, or with fewer than
+// 32 + d / 4 others, takes its products on the fp32 MFMA too, in a second pass
+// over its tiles if others share them (tanh of an N(0, 1) sum: one row in 7e8 / d).
 //
 // Bound: at d = 1024, |V| = 32000 a step of up to 64 rows by streaming W_out
 // (131 MB at 5.4 TB/s: 24.4 us, was 31.0), larger ones by the fp16 MFMA at
@@ -177,7 +181,7 @@ __device__ __forceinline__ void fp32_mainloop(unsigned char (*stage)[NBM * SPLIT
     for (int r = 0; r < 16; ++r) tot[b][r] = first[b][r] + tot[b][r];
 }
 
-// What k_split_wout found in W_out besides plain rows (bits of *w_kinds).
+// What k_split_wout found in W_out besides plain rows (bits of DevCtrl::w_kinds).
 constexpr int KIND_FAR = 1, KIND_FP32 = 2;
 
 // Tile: vocabulary tile vt x NB blocks of 32 rows from row r0.
@@ -187,18 +191,37 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = vt * 4 + wv;
-  f16v tot[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) tot[b] = f16v{};
   const float *states = static_cast<const float *>(st.proj_in);   // under 4 GiB
-  auto row_at = [&](int b) { return (uint32_t)min(r0 + 32 * b + (lane & 31), R - 1) * (uint32_t)st.d; };
-  if (!PLAIN && split_tile_fp32(st, vt)) {
-    const float *w = static_cast<const float *>(st.W_out) + (size_t)min(32 * slice + (lane & 31), st.V - 1) * st.d;
-    uint32_t row[NB];
+  // The lane, and the offset of its row of block b: formed anew for each use, as
+  // the K loops leave no register to keep them in.
+  auto lane_again = [&] {
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  auto row_at = [&](int b, int l) { return (uint32_t)min(r0 + 32 * b + (l & 31), R - 1) * (uint32_t)st.d; };
+  // Which of the tile's rows need the fp32 MFMA (the same in every wave).
+  bool all = false, some = false;
+  if constexpr (!PLAIN) {
+    bool any = false, every = true;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) row[b] = row_at(b) + 16 * h;
-    fp32_mainloop<NB>(sm.stage, w + 16 * h, states + 4 * wv, row, st.d, tot);
-  } else {
+    for (int b = 0; b < NB; ++b) {
+      const bool f = split_row_fp32(st, min(r0 + 32 * b + (lane & 31), R - 1));
+      any |= f;
+      every &= f;
+    }
+    all = split_tile_fp32(st, vt) || __all(every);
+    some = all || __any(any);
+  }
+  auto finish = [&](f16v *tot, auto &&wanted) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
+    tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R, wanted);
+  };
+  if (!all) {
+    f16v tot[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) tot[b] = f16v{};
     const int nch = st.d / SPLIT_K;
     const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
     split_mainloop<NB, D>(sm.stage, st.wout_t + (size_t)slice * nch * SPLIT_CHUNK + lane * 16,
@@ -207,15 +230,27 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
 #pragma unroll
     for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
     if (const int nfar = PLAIN ? 0 : st.w_nfar[slice]) {
-      const float *x[NB];
+      uint32_t row[NB];
+      const int l = lane_again();
 #pragma unroll
-      for (int b = 0; b < NB; ++b) x[b] = states + row_at(b);
-      add_far<NB>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, h, x, tot);
+      for (int b = 0; b < NB; ++b) row[b] = row_at(b, l);
+      add_far<NB>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, h, states, row, tot);
     }
+    finish(tot, [](int) { return true; });
   }
+  if constexpr (!PLAIN) {
+    if (!some) return;
+    f16v tot[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
-  tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R);
+    for (int b = 0; b < NB; ++b) tot[b] = f16v{};
+    const int l = lane_again(), k0 = 16 * (l >> 5);
+    const float *w = static_cast<const float *>(st.W_out) + (size_t)min(32 * slice + (l & 31), st.V - 1) * st.d + k0;
+    uint32_t row[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) row[b] = row_at(b, l) + k0;
+    fp32_mainloop<NB>(sm.stage, w, states + 4 * wv, row, st.d, tot);
+    finish(tot, [&](int r) { return all || split_row_fp32(st, r); });
+  }
 }
 
 // Blocks per row tile for a step of R rows: the count that minimizes the
@@ -247,8 +282,8 @@ __device__ __forceinline__ int split_tile_blocks(int R, int S, int n_cu) {
 // the row tiles of one vocabulary tile run side by side on one XCD and share
 // its L2 copy of the W_out tile; rounds alternate direction, so that a
 // workgroup which drew a full row tile draws a partial one in the next.
-// A W_out of plain rows only (most are) has a walk of its own: a kind looked up
-// per tile, ahead of its K loop, cost 0.3 us per step.
+// A step of plain rows only, of W_out and of states (most are), has a walk of its
+// own: a kind looked up per tile, ahead of its K loop, cost 0.3 us per step.
 template <int KB, bool PLAIN>
 __device__ __forceinline__ void split_walk(const DevState &st, SplitSmem<KB> &sm, int R) {
   const int bt = split_tile_blocks(R, st.S, st.n_cu);
@@ -275,8 +310,8 @@ __device__ __forceinline__ void split_walk(const DevState &st, SplitSmem<KB> &sm
 
 template <int KB>
 __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
-  const int R = st.ctrl->R, kinds = *st.w_kinds;
-  if (R <= 0 || kinds < 0) return;   // kinds is 0 or above: tested here so that both loads are one wait
+  const int R = st.ctrl->R, kinds = st.ctrl->w_kinds | st.ctrl->far;
+  if (R <= 0 || kinds < 0) return;   // kinds is 0 or above: tested here so that the loads are one wait
   __shared__ SplitSmem<KB> sm;
   if (kinds == 0) split_walk<KB, true>(st, sm, R);
   else split_walk<KB, false>(st, sm, R);
@@ -288,7 +323,7 @@ __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
 // the largest value where that leaves none below it, else lies where it holds
 // most (top is held to [36, 254], so that the factors below are normal
 // numbers). With e = top - 126, values are multiplied by 2^(15 - e) and a sum
-// of products with 2^14-scaled states by 2^(e - 29). Layout: [S][4 slices]
+// of products with 2^15-scaled states by 2^(e - 30). Layout: [S][4 slices]
 // [d / 64 chunks][4 steps][hi, lo][64 lanes][8 fp16], lane (h, l) of step s
 // holding k = 64 chunk + 16 s + 8 h .. + 7 of vocabulary row
 // 128 vt + 32 slice + l (zero past V, and for far values).
@@ -391,12 +426,12 @@ __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
   }
   if (part == 0) {
     tops[row] = top;
-    st.w_scale[vb + row] = ldexpf(1.0f, top - 126 - 29);
+    st.w_scale[vb + row] = ldexpf(1.0f, top - 126 - 30);
   }
   const bool fp32 = __syncthreads_or(few) || nfar > SPLIT_FAR;
   if (tid == 0) {
     st.w_nfar[blockIdx.x] = fp32 ? -1 : nfar;
-    if (fp32 || nfar > 0) atomicOr(st.w_kinds, fp32 ? KIND_FP32 : KIND_FAR);
+    if (fp32 || nfar > 0) atomicOr(&st.ctrl->w_kinds, fp32 ? KIND_FP32 : KIND_FAR);
   }
   const int v = vb + (lane & 31), vtop = tops[lane & 31];
   const float up = ldexpf(1.0f, 15 + 126 - vtop);

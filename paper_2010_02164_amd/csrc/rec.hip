@@ -128,8 +128,16 @@ __device__ __forceinline__ void rec_tile_f32(const DevState &st, float (*red)[RT
       _Float16 f[2];
       uint32_t u;
     } hi, lo;
+    int far = 0;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) split_f16(hv[q] * SPLIT_H_SCALE, hi.f[q], lo.f[q]);
+    for (int q = 0; q < 2; ++q) {
+      split_f16(hv[q] * SPLIT_H_SCALE, hi.f[q], lo.f[q]);
+      far += fabsf(hv[q]) < SPLIT_H_MIN ? (hv[q] == 0.0f ? 1 : d) : 0;
+    }
+    if (far) {   // rare
+      atomicAdd(&st.r_far[row], far);
+      st.ctrl->far = 1;
+    }
     unsigned char *sp = st.hsplit + split_state_off(d, row, v0 + i0);
     *reinterpret_cast<uint32_t *>(sp) = hi.u;
     *reinterpret_cast<uint32_t *>(sp + 1024) = lo.u;

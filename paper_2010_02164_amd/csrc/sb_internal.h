@@ -39,11 +39,12 @@ struct DevCtrl {
   int32_t n_queued;   // inputs submitted so far
   int32_t cursor;     // next input to admit (Alg. 1's c)
   int32_t R;          // rows (active candidates) expanded this step
+  int32_t far;        // 1: a row of this step is counted in DevState::r_far
+  int32_t w_kinds;    // fp32: 0, or what W_out holds besides plain rows (proj_f32.hip); kept by a reset
   int32_t t_sel;      // smallest 1-based output position among the selected beams
   int32_t live;       // live beams after admission
   int32_t done;       // 1: nothing queued and no beam live
   int32_t n_sel;      // beams selected this step
-  int32_t pad0;
   int64_t timesteps, expansions, noops, refills, admitted, hyps, finished;
   int64_t positions;       // output positions t of the expanded rows, summed
   int64_t tile_recomputes; // (row, tile) pairs recomputed by the row merge
@@ -140,8 +141,8 @@ struct DevState {
   float *w_scale;          // fp32: [S * 128]
   int32_t *w_nfar;         // fp32: [S * 4] far values of a 32-row slice, -1: the slice needs the fp32 MFMA
   FarValue *w_far;         // fp32: [S * 4][SPLIT_FAR]
-  int32_t *w_kinds;        // fp32: 0, or what W_out holds besides plain rows (proj_f32.hip)
   unsigned char *hsplit;   // fp32: the step's new states split (split_state_off)
+  int32_t *r_far;          // fp32: [R_max] new states of the row that the pairs do not suit (split_row_fp32)
   // sizes and parameters
   int32_t n, k, d, V, M, max_len_cap, refill_thr, S, R_max, dtype, kv_layers, max_inputs;
   int32_t attn;        // 1: projection input = h + layer-mean attention read-out

@@ -381,6 +381,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     st.r_y[r] = steps == 0 ? 0 : y;                 // and the start symbol
     st.r_t[r] = steps + 1;
     st.r_Lx[r] = x.lx;
+    if (st.r_far) st.r_far[r] = 0;
     if (st.rec_i8) {
       st.haux[r].F = 1;
       st.haux[r].n = 0;
@@ -401,6 +402,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     c->cursor = cursor + admit;
     c->live = live + admit;
     c->R = R;
+    c->far = 0;
     c->n_sel = nsel;
     c->t_sel = R > 0 ? mn + 1 : 0;
     c->done = R == 0 ? 1 : 0;
@@ -435,10 +437,10 @@ __global__ void k_init(DevState st, bool create) {
     st.s_status[i] = SLOT_EMPTY;
   }
   if (i < st.max_inputs) st.o_count[i] = 0;
-  if (i == 0 && create && st.w_kinds) *st.w_kinds = 0;   // set by the split of W_out that follows
   if (i == 0) {
     DevCtrl z = {};
     z.done = 1;
+    z.w_kinds = create ? 0 : st.ctrl->w_kinds;   // set by the split of W_out that follows
     *st.ctrl = z;
   }
 }

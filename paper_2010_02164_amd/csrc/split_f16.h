@@ -10,7 +10,8 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr int SPLIT_K = 64;                        // K values per chunk
 constexpr int SPLIT_CHUNK = SPLIT_K / 16 * 2048;   // bytes of a 32-row block's chunk: [4 steps][hi, lo][64 lanes][16 B]
-constexpr float SPLIT_H_SCALE = 16384.0f;          // states are split after scaling by 2^14 (|h| <= 1)
+constexpr float SPLIT_H_SCALE = 32768.0f;          // states are split after scaling by 2^15 (|h| <= 1)
+constexpr float SPLIT_H_MIN = 1.0f / (1 << 29);    // smallest state that the pairs hold
 constexpr float SPLIT_LO = 4096.0f;                // scale of the low parts
 
 // x = hi + lo / 4096. x - hi has at most 13 significant bits, so the pair is x
@@ -62,6 +63,12 @@ __device__ __forceinline__ bool split_tile_fp32(const DevState &st, int vt) {
   return (n.x | n.y | n.z | n.w) < 0;
 }
 
+// Whether a row's products are: r_far counts its states that are zero, once, and
+// those below SPLIT_H_MIN, d times.
+__device__ __forceinline__ bool split_row_fp32(const DevState &st, int row) {
+  return st.r_far[row] > st.d - split_min_terms(st.d);
+}
+
 // The 16 vocabulary rows' scales of a lane (register r: row 8 (r / 4) + r % 4
 // from `p`).
 struct SplitScale {
@@ -79,12 +86,13 @@ struct SplitScale {
 };
 
 // z[b] += the far values of a 32-row vocabulary slice (entries f[0..n)) times
-// row b's state, one fused product each in list order. The caller's lane half h
+// row b's state (x + row[b]), one fused product each in list order. The caller's lane half h
 // holds vocabulary rows 8 (r / 4) + 4 h + r % 4 of the slice in registers r.
 // The states of four entries are loaded at a time (past the end the last
 // entry's).
 template <int NB>
-__device__ __forceinline__ void add_far(const FarValue *f, int n, int h, const float *const *x, f16v *z) {
+__device__ __forceinline__ void add_far(const FarValue *f, int n, int h, const float *x, const uint32_t *row,
+                                        f16v *z) {
   constexpr int U = 4;
 #pragma unroll 1
   for (int i0 = 0; i0 < n; i0 += U) {
@@ -99,12 +107,12 @@ __device__ __forceinline__ void add_far(const FarValue *f, int n, int h, const f
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) hv[u][b] = x[b][at[u] & 0xFFFF];
+      for (int b = 0; b < NB; ++b) hv[u][b] = (x + (at[u] & 0xFFFF))[row[b]];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (i0 + u >= n) break;
-      const int row = at[u] >> 16, reg = 4 * (row >> 3) + (row & 3);
-      const bool mine = ((row >> 2) & 1) == h;
+      const int v = at[u] >> 16, reg = 4 * (v >> 3) + (v & 3);
+      const bool mine = ((v >> 2) & 1) == h;
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (r == reg) {

@@ -305,16 +305,19 @@ def test_expand_one_lane_holds_the_best(gpu, cfg_i, k, per_tile):
 # to its own are the logits of the other 15. They are compared with 64-bit
 # products of W_out and the states the step returned, as a multiple of 2^-24 of
 # the products' sum of magnitudes.
-ON, OFF, FAINT = 3, 7, 11   # units that are 1, 0 and 1e-20 in every row
+ON, OFF, FAINT = 3, 7, 11   # units that are 1, 0 and 2^-27 in every row
 
 
-def _logit_case(V, d, R, make, one_tile, seed=91):
+def _logit_case(V, d, R, make, one_tile, seed=91, states=None):
     """(logits [R, 15], 64-bit logits, sums of magnitudes): the 15 chosen rows
-    are make(rng, dense rows [15, d]); all in one 128-token tile or spread."""
+    are make(rng, dense rows [15, d]); all in one 128-token tile or spread. With
+    `states`, E and W_h are what it makes of them."""
     rng = np.random.default_rng(seed)
     wl = make_workload(scaled(1, N=4, V=V, d=d, k=16, M=16, n=-(-R // 16)))
     E, Wh, W = wl.E.copy(), wl.W_h.copy(), wl.W_out.copy()
-    for u, e in ((ON, 40.0), (OFF, 0.0), (FAINT, 1e-20)):
+    if states:
+        E, Wh = states(rng, E, Wh)
+    for u, e in ((ON, 40.0), (OFF, 0.0), (FAINT, 2.0**-27)):
         Wh[u], E[:, u] = 0.0, e
     W[:, ON] = -50.0
     at = 128 * (V // 256) + 5 + (7 * np.arange(16) if one_tile else 0)
@@ -323,7 +326,7 @@ def _logit_case(V, d, R, make, one_tile, seed=91):
     rows[:, [ON, OFF, FAINT]] = 0.0
     W[toks[0]] = 0.0
     W[toks[1:]] = make(rng, rows).astype(np.float32)
-    wl = dataclasses.replace(wl, E=E, W_h=Wh, W_out=W.astype(np.float32))
+    wl = dataclasses.replace(wl, E=E.astype(np.float32), W_h=Wh.astype(np.float32), W_out=W.astype(np.float32))
     _, _, _, _, h, _, lp, tok, _, _ = _expand_case(wl, R, seed)
     order = np.argsort(tok, axis=1)
     assert np.array_equal(np.take_along_axis(tok, order, 1), np.tile(np.sort(toks), (R, 1)))
@@ -365,7 +368,7 @@ def _octaves(lo, hi, some=None):
 WIDE_ROWS = [
     ("plain", lambda rng, rows: rows, 6), ("scaled", lambda rng, rows: rows * 2.0 ** rng.integers(-15, 1, (15, 1)), 6),
     ("mask_1e9", _set([OFF], -1e9), 6), ("mask_1e12", _set([OFF], -1e12), 6), ("mask_3e38", _set([OFF], -3e38), 6),
-    ("two_masks_up", _set([OFF, FAINT], [1e21 * 2.0**-i for i in range(15)]), 6), ("faint", _set([FAINT], -1e21), 6),
+    ("two_masks_up", _set([OFF, FAINT], [2.0**(30 - i) for i in range(15)]), 6), ("faint", _set([FAINT], -2.0**30), 6),
     ("tiny_values", _octaves(-50, -40, 3), 6), ("octaves", _octaves(-90, 0), 6), ("subnormal", _octaves(-140, -135, 80), 6),
     ("one_term", _keep(1), 1), ("two_terms", _keep(2), 2), ("forty_terms", _keep(40), 6),
 ]
@@ -387,3 +390,68 @@ def test_expand_f32_wide_rows(gpu, name, make, units, V, d):
         assert np.all(np.abs(z - ref) <= units * 2.0**-24 * mag + 2.0**-44)
         got.append(z)
     assert np.abs(got[0] - got[1]).max() <= 2.0**-44
+
+
+def _scaled_states(e):
+    return lambda rng, E, Wh: (E * 2.0**e, Wh * 2.0**e)
+
+
+def _tiny_units(rng, E, Wh):   # some units far below the others
+    u = rng.choice(np.arange(12, E.shape[1]), 6, replace=False)
+    E[:, u], Wh[u] = E[:, u] * 2.0**-40, 0.0
+    return E, Wh
+
+
+def _few_units(n):
+    def make(rng, E, Wh):   # n units that are not 0, with the ones of every row
+        off = rng.permutation(np.setdiff1d(np.arange(E.shape[1]), [ON, OFF, FAINT]))[n:]
+        E[:, off], Wh[off] = 0.0, 0.0
+        return E, Wh
+    return make
+
+
+SMALL_STATES = [("2^-20", _scaled_states(-20), 20, 6), ("2^-26", _scaled_states(-26), 26, 6),
+                ("2^-34", _scaled_states(-34), 34, 6), ("2^-60", _scaled_states(-60), 60, 6),
+                ("tiny_units", _tiny_units, 0, 6), ("one_unit", _few_units(1), 0, 1), ("two_units", _few_units(2), 0, 2)]
+
+
+@pytest.mark.parametrize("V,d", [(1000, 64), (8320, 256), (8320, 1024)])
+@pytest.mark.parametrize("name,states,up,units", SMALL_STATES, ids=[c[0] for c in SMALL_STATES])
+def test_expand_f32_small_states(gpu, name, states, up, units, V, d):
+    """States smaller than the fp16 pairs hold, or few that are not zero, give
+    their logits as the fp32 MFMA did (W_out is scaled up by as much)."""
+    got = []
+    for one_tile in (False, True):
+        z, ref, mag = _logit_case(V, d, 45, lambda rng, rows: rows * 2.0**up, one_tile, states=states)
+        err = np.abs(z - ref) / mag * 2.0**24
+        print(f"[expand] f32 states {name} V={V} d={d} one_tile={one_tile}: {err.max():.2f} units", flush=True)
+        assert np.all(np.abs(z - ref) <= units * 2.0**-24 * mag + 2.0**-44)
+        got.append(z)
+    assert np.abs(got[0] - got[1]).max() <= 2.0**-44
+
+
+@pytest.mark.parametrize("V,k,R", [(1000, 4, 70), (8320, 12, 200)])
+def test_expand_f32_rows_of_both_kinds(gpu, V, k, R):
+    """Rows that need the fp32 MFMA change no bit of the rows that share their
+    step, whose results are those of a step without them."""
+    import torch
+    from paper_2010_02164_amd import decoder_for_workload
+    d = 256
+    wl = make_workload(scaled(1, N=4, V=V, d=d, k=k, M=k, n=-(-R // k)))
+    E, Wh = wl.E.copy(), np.zeros_like(wl.W_h)
+    E[1::2] *= np.float32(2.0**-33)      # states of odd tokens
+    wl = dataclasses.replace(wl, E=E, W_h=Wh)
+    rng = np.random.default_rng(95)
+    y = rng.integers(0, V, R).astype(np.int32)
+    y[:40] &= ~1                         # a block of plain rows, then both kinds
+    t = rng.integers(1, 40, R).astype(np.int32)
+    h = torch.zeros(R, d, device="cuda")
+    dec = decoder_for_workload(wl, max_inputs=4)
+    print(f"[expand] f32 rows of both kinds V={V} R={R}", flush=True)
+    h1, lse, lp, tok = dec.debug_expand(h, y, t, t)
+    for part in (y & 1 == 0, y & 1 == 1):
+        n = int(part.sum())
+        h2, lse2, lp2, tok2 = dec.debug_expand(h[:n].contiguous(), y[part], t[part], t[part])
+        assert torch.equal(h1[torch.from_numpy(part).cuda()], h2)
+        assert np.array_equal(lse[part], lse2) and np.array_equal(lp[part], lp2) and np.array_equal(tok[part], tok2)
+    dec.close()
