@@ -116,9 +116,8 @@ def test_cfg5_kv_rows(gpu, sched):
 
 
 def test_bf16_schedulers_agree_bitwise_across_tile_shapes(gpu):
-    # |V| = 32000 with steps of up to 640 rows: large steps use 256-wide
-    # vocabulary tiles, small ones 128-wide tiles of 1 to 8 blocks; a row's
-    # sums must not depend on which.
+    # |V| = 32000 with steps of up to 640 rows: row tiles of 1 to 4 blocks of 32,
+    # by the step's rows; a row's sums must not depend on which.
     wl = make_workload(scaled(4, N=96, n=64, V=32000, d=256))
     a, sa, da = gpu_decode(wl, "var_batch")
     counts, width = da.rows_histogram()
@@ -130,6 +129,6 @@ def test_bf16_schedulers_agree_bitwise_across_tile_shapes(gpu):
             assert [(h.tokens, h.score, h.status) for h in ya] == [(h.tokens, h.score, h.status) for h in yb]
 
 
-def test_cfg4_wide_tiles_parity(gpu):
+def test_cfg4_large_steps_parity(gpu):
     wl = make_workload(scaled(4, N=96, n=64, V=32000, d=256))
     check_parity(wl, "var_stream")
