@@ -78,8 +78,8 @@ def test_expand_f32(gpu, cfg_i, R, over):
 @pytest.mark.parametrize("over", [dict(V=8000, n=32), dict(V=4160, d=256, n=16, k=16),
                                   dict(V=32000, n=64), dict(V=32128, d=256, n=64)])
 def test_expand_bf16(gpu, over):
-    # The last two use 256-wide vocabulary tiles (640 rows fill a round of
-    # them); 32128 tokens leave the last 256-wide tile half empty.
+    # The last two fill several rounds of tiles of 4 row blocks, over an even
+    # and an odd number of vocabulary tiles.
     wl = make_workload(scaled(4, N=4, **over))
     _, _, _, _, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, 640 if over["V"] >= 32000 else 200, 12)
     print(f"[expand] bf16 {over}", flush=True)
@@ -164,39 +164,46 @@ def test_decode_bf16_small_values(gpu, long_row):
 
 
 # The fp32 projection splits W_out rows and states into fp16 pairs after a
-# power-of-two scaling per W_out row. Rows of very different magnitude, an
-# outlier inside a row, a zero row and a row of subnormals keep each logit
-# within a few units of 2^-24 of its products' sum of magnitudes.
+# power-of-two scaling per W_out row. Large rows and an outlier inside a row keep
+# each returned logit within a few units of 2^-24 of its products' sum of
+# magnitudes (rows smaller than the others, which these outrank:
+# test_expand_f32_wide_rows).
 @pytest.mark.parametrize("V,d,R,k", [(130, 64, 1, 4), (1000, 192, 33, 12), (8320, 320, 97, 5), (32000, 64, 161, 8)])
 def test_expand_f32_row_scales(gpu, V, d, R, k):
     rng = np.random.default_rng(41)
     wl = make_workload(scaled(1, N=4, V=V, d=d, k=k, M=k, n=-(-R // k)))
     W = wl.W_out.copy()
     W[1] *= 2.0**12
-    W[2] *= 2.0**-30
-    W[3] = 0.0
-    W[4] = 1e-41
     W[5, d // 2] = 700.0
     W[V - 1] *= 2.0**8
     W[6:64] *= 2.0 ** rng.integers(-8, 6, 58)[:, None]
     W = W.astype(np.float32)
     wl = dataclasses.replace(wl, W_out=W)
-    _, _, t, Lx, h_gpu, lse, lp, tok, h_ref, lp_ref = _expand_case(wl, R, 42)
+    _, _, t, Lx, h_gpu, lse, lp, tok, _, _ = _expand_case(wl, R, 42)
     print(f"[expand] f32 row scales V={V} d={d} R={R}", flush=True)
-    z = h_ref @ W.astype(np.float64).T
+    # Against the logits of the states that the step returned. Per logit: 6
+    # units (WIDE_ROWS, below) and, for EOS, the bias' rounding; the log-sum-exp
+    # is off by the logits' errors, weighted by their probabilities, plus its own
+    # fp32 sum over |V| terms.
+    h, Wd = h_gpu.astype(np.float64), W.astype(np.float64)
+    z = h @ Wd.T
     z[:, 0] += wl.cfg.beta * (t - Lx)
-    # Per logit: the state's own fp32 error (as in _check_rows, times |w|) and
-    # sqrt(d) roundings of the sum; the log-sum-exp is off by at most the
-    # largest logit's error, plus its own fp32 sum over |V| terms.
-    mag = np.abs(W.astype(np.float64))
-    per_v = (8 * np.sqrt(d) * 2.0**-24 * 4) * np.sqrt((mag**2).sum(1)) + 8 * np.sqrt(d) * 2.0**-24 * (
-        np.abs(h_ref) @ mag.T)
-    tol = per_v.max(1) + 2e-5
-    got = np.take_along_axis(lp_ref, tok, 1)
-    kth = -np.sort(-lp_ref, axis=1)[:, :k]
-    assert np.all(np.abs(lp - got) < tol[:, None])
-    assert np.all(np.abs(-np.sort(-got, axis=1) - kth) < tol[:, None])
+    err = 6 * 2.0**-24 * (np.abs(h) @ np.abs(Wd).T)
+    # One product makes up row 5's sum from the middle on: its d / 2 later
+    # additions round by up to half a unit of it each (0.3 rms, times 4).
+    err[:, 5] *= 1 + 1.2 * np.sqrt(d / 2) / 6
+    err[:, 0] += 2.0**-24 * np.abs(z[:, 0])
+    m = z.max(1, keepdims=True)
+    ref_lse = m[:, 0] + np.log(np.exp(z - m).sum(1))
+    lse_err = (np.exp(z - ref_lse[:, None]) * err).sum(1) + 1e-5
+    assert np.all(np.abs(lse - ref_lse) < lse_err)
+    assert np.all(np.abs(lp + lse[:, None] - np.take_along_axis(z, tok, 1)) <= np.take_along_axis(err, tok, 1) + 1e-12)
     assert np.all(np.diff(lp, axis=1) <= 1e-12)
+    # No token left out is above one returned by more than their errors.
+    low = np.take_along_axis(z + err, tok, 1).min(1)
+    rest = z - err
+    np.put_along_axis(rest, tok, -np.inf, 1)
+    assert np.all(rest.max(1) <= low)
 
 
 @pytest.mark.parametrize("V,d", [(1000, 64), (8320, 192)])
@@ -362,11 +369,19 @@ def _octaves(lo, hi, some=None):
     return make
 
 
+def _mixed(rng, rows):   # a tiny row, a zero one, and ordinary ones
+    rows = rows * 2.0 ** rng.integers(-8, 3, (15, 1))
+    rows[0] *= 2.0**-30
+    rows[1] = 0.0
+    return rows
+
+
 # Units of 2^-24: a sum of n products rounded once per product is off by at most
 # n; of many products by about 2.2 at most over these samples on the fp32 MFMA,
 # and by up to 3.8 from pairs of fp16 (2^-21.2 = 7 for a single product).
 WIDE_ROWS = [
     ("plain", lambda rng, rows: rows, 6), ("scaled", lambda rng, rows: rows * 2.0 ** rng.integers(-15, 1, (15, 1)), 6),
+    ("mixed", _mixed, 6), ("subnormal_rows", lambda rng, rows: 0 * rows + 1e-41, 6),
     ("mask_1e9", _set([OFF], -1e9), 6), ("mask_1e12", _set([OFF], -1e12), 6), ("mask_3e38", _set([OFF], -3e38), 6),
     ("two_masks_up", _set([OFF, FAINT], [2.0**(30 - i) for i in range(15)]), 6), ("faint", _set([FAINT], -2.0**30), 6),
     ("tiny_values", _octaves(-50, -40, 3), 6), ("octaves", _octaves(-90, 0), 6), ("subnormal", _octaves(-140, -135, 80), 6),
@@ -384,7 +399,7 @@ def test_expand_f32_wide_rows(gpu, name, make, units, V, d):
     got = []
     for one_tile in (False, True):
         z, ref, mag = _logit_case(V, d, 45, make, one_tile)
-        err = np.abs(z - ref) / mag * 2.0**24
+        err = np.abs(z - ref) / np.maximum(mag, 2.0**-20) * 2.0**24
         print(f"[expand] f32 {name} V={V} d={d} one_tile={one_tile}: {err.max():.2f} units", flush=True)
         # lp are doubles of up to 200: differences carry 2^-45 of their own
         assert np.all(np.abs(z - ref) <= units * 2.0**-24 * mag + 2.0**-44)
@@ -454,4 +469,32 @@ def test_expand_f32_rows_of_both_kinds(gpu, V, k, R):
         h2, lse2, lp2, tok2 = dec.debug_expand(h[:n].contiguous(), y[part], t[part], t[part])
         assert torch.equal(h1[torch.from_numpy(part).cuda()], h2)
         assert np.array_equal(lse[part], lse2) and np.array_equal(lp[part], lp2) and np.array_equal(tok[part], tok2)
+    dec.close()
+
+
+@pytest.mark.parametrize("kind", ["plain", "far", "fp32"])
+def test_expand_f32_rows_do_not_depend_on_the_step(gpu, kind):
+    """A row's bits are the same in steps of every tile height and of more than
+    one group of row tiles, on each of the projection's ways."""
+    import torch
+    from paper_2010_02164_amd import decoder_for_workload
+    V, d, R, k = 8320, 1024, 700, 12
+    wl = make_workload(scaled(1, N=4, V=V, d=d, k=k, M=k, n=-(-R // k)))
+    W = wl.W_out.copy()
+    if kind == "far":
+        W[np.arange(V), np.arange(V) % d] = -2.0**40
+    elif kind == "fp32":
+        W[::128, 100:] = 0.0
+    rng = np.random.default_rng(97)
+    h = torch.from_numpy(np.tanh(rng.standard_normal((R, d))).astype(np.float32)).cuda()
+    y, t = rng.integers(0, V, R).astype(np.int32), rng.integers(1, 40, R).astype(np.int32)
+    dec = decoder_for_workload(dataclasses.replace(wl, W_out=W), max_inputs=4)
+    print(f"[expand] f32 {kind} rows in steps of several sizes", flush=True)
+    whole = dec.debug_expand(h, y, t, t)
+    for n in (1, 33, 65, 97, 129, 385):
+        for r0 in (0, R - n):
+            part = dec.debug_expand(h[r0:r0 + n].contiguous(), y[r0:r0 + n], t[r0:r0 + n], t[r0:r0 + n])
+            assert torch.equal(part[0], whole[0][r0:r0 + n])
+            for a, b in zip(part[1:], whole[1:]):
+                assert np.array_equal(a, b[r0:r0 + n]), (n, r0)
     dec.close()
