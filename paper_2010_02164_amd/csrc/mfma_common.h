@@ -23,21 +23,6 @@ __device__ __forceinline__ const unsigned char *state_row(const DevState &st, in
 // Number of workgroups to launch for G tiles: a multiple of the 8 XCDs.
 __host__ __device__ inline int xcd_grid(int G) { return (G + 7) / 8 * 8; }
 
-// XCD-aware tile order. Workgroup ids are dealt round robin to the 8 XCDs;
-// remap so that each XCD walks a contiguous range of tiles in which the
-// row-tile index varies fastest: workgroups sharing one weight tile then
-// share that XCD's L2. Returns false for the padding workgroups.
-__device__ __forceinline__ bool tile_of(int nvt, int nrt, int &vt, int &rt) {
-  const int G = nvt * nrt;
-  const int Gp = xcd_grid(G);
-  const int g = blockIdx.x;
-  const int lin = (g & 7) * (Gp >> 3) + (g >> 3);
-  if (lin >= G) return false;
-  vt = lin / nrt;
-  rt = lin - vt * nrt;
-  return true;
-}
-
 __device__ __forceinline__ float bf16f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 }  // namespace sb

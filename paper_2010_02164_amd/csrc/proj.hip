@@ -29,7 +29,7 @@
 // W_out is streamed straight into registers from a copy laid out in MFMA
 // fragment order (one coalesced 1 KB load per wave and fragment), kept D
 // chunks ahead; the states pass through a double-buffered LDS tile shared by
-// the waves, loaded D chunks ahead as well.
+// the waves, one chunk ahead in registers and one in LDS.
 // Blocks of 32 rows past R are neither loaded nor computed.
 #include <algorithm>
 

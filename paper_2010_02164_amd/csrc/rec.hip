@@ -309,16 +309,11 @@ __device__ __forceinline__ AuxRegs load_aux(const RowAux *ax) {
   return r;
 }
 
-// Digit planes (rec_dig_off layout) and list of the state feeding row r.
+// Digit planes (rec_dig_off layout) of the state feeding row r.
 __device__ __forceinline__ const int8_t *row_digits(const DevState &st, int r) {
   const int src = st.r_hsrc[r];
   return (src >= 0 ? st.s_hd : st.q_hd) + (size_t)(src >= 0 ? src : -1 - src) * rec_dig_row_bytes(st.d);
 }
-__device__ __forceinline__ const RowAux *row_aux(const DevState &st, int r) {
-  const int src = st.r_hsrc[r];
-  return src >= 0 ? st.s_haux + src : st.q_haux + (-1 - src);
-}
-
 __device__ __forceinline__ bool w_in_window(uint32_t b, int Ew) {
   const uint32_t e8 = (b >> 7) & 0xFFu;
   return (b & 0x7FFFu) == 0u || (int)max(e8, 1u) - 113 - Ew >= 0;

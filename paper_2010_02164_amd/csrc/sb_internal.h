@@ -91,7 +91,7 @@ struct DevState {
   int32_t *r_Lx;       // L_x of the row's input (EOS bias)
   double *r_lse;       // log-sum-exp of the row's logits
   void *hbuf;          // [R_max][d] new states of the expanded rows
-  float *part;         // [R_max][S][2 + 2k] per-tile (max, sumexp, top-k vals, top-k ids)
+  float *part;         // [R_max][S][part_width(tile_keys)] per-tile (max, sum exp, best keys as two words each)
   double *top_lp;      // [R_max][k] log-probs of each row's best k tokens
   int32_t *top_tok;    // [R_max][k]
   // outputs, indexed by queue position
@@ -172,9 +172,7 @@ constexpr int REC_WTILE = 64;
 __host__ __device__ constexpr int rec_dig_off(int k, int a) { return (k >> 5) * 128 + ((k >> 4) & 1) * 48 + a * 16 + (k & 15); }
 constexpr size_t rec_dig_row_bytes(size_t d) { return 4 * d; }
 
-// Tile sizes of the projection/recurrence GEMMs.
-constexpr int GEMM_BV = 128;   // out features (vocab / hidden) per workgroup
-constexpr int GEMM_BR = 64;    // batch rows per workgroup
+constexpr int GEMM_BV = 128;   // vocabulary rows (or KV outputs) per projection tile
 
 inline int proj_tiles(int V) { return (V + GEMM_BV - 1) / GEMM_BV; }
 

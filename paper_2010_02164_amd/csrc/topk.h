@@ -94,16 +94,6 @@ __device__ __forceinline__ void topk_merge(TopK<K> &a, const TopK<K> &b) {
       if ((j & s) == 0) cex(a.k[j], a.k[j + s], true);
 }
 
-template <int K>
-__device__ __forceinline__ void topk_shfl_xor(TopK<K> &out, const TopK<K> &in, int mask) {
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const uint32_t lo = __shfl_xor((uint32_t)in.k[j], mask, 64);
-    const uint32_t hi = __shfl_xor((uint32_t)(in.k[j] >> 32), mask, 64);
-    out.k[j] = ((cand_key)hi << 32) | lo;
-  }
-}
-
 // Stored as two 32-bit words (low, high) in a float array.
 template <int K>
 __device__ __forceinline__ void topk_store(float *p, const TopK<K> &t) {
@@ -150,17 +140,6 @@ __device__ __forceinline__ void top4_of_16(cand_key *a, TopK<4> &out) {
   topk_merge(g[2], g[3]);
   topk_merge(g[0], g[2]);
   out = g[0];
-}
-
-// Insert one key into a sorted list (the smallest key falls off).
-template <int K>
-__device__ __forceinline__ void topk_insert(TopK<K> &t, cand_key x) {
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const cand_key hi = t.k[j] > x ? t.k[j] : x;
-    x = t.k[j] > x ? x : t.k[j];
-    t.k[j] = hi;
-  }
 }
 
 // (m, s) represents log(s) + m: a running max and a sum of exp(z - m).
