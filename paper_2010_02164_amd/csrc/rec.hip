@@ -10,6 +10,7 @@
 #include "bf16_round.h"
 #include "mfma_common.h"
 #include "split_f16.h"
+#include "wave.h"
 
 namespace sb {
 namespace {
@@ -134,9 +135,14 @@ __device__ __forceinline__ void rec_tile_f32(const DevState &st, float (*red)[RT
       split_f16(hv[q] * SPLIT_H_SCALE, hi.f[q], lo.f[q]);
       far += fabsf(hv[q]) < SPLIT_H_MIN ? (hv[q] == 0.0f ? 1 : d) : 0;
     }
-    if (far) {   // rare
-      atomicAdd(&st.r_far[row], far);
-      st.ctrl->far = 1;
+    // Rare; one add per row and tile (a row's 16 threads are neighbouring lanes).
+    if (const unsigned long long any = __ballot(far != 0)) {
+      far += (int)dpp_partner<0>((uint32_t)far);
+      far += (int)dpp_partner<1>((uint32_t)far);
+      far += (int)dpp_partner<2>((uint32_t)far);
+      far += (int)dpp_partner<3>((uint32_t)far);
+      if ((threadIdx.x & 15) == 0 && far) atomicAdd(&st.r_far[row], far);
+      if (lane == __ffsll((long long)any) - 1) st.ctrl->far = 1;
     }
     unsigned char *sp = st.hsplit + split_state_off(d, row, v0 + i0);
     *reinterpret_cast<uint32_t *>(sp) = hi.u;
