@@ -188,16 +188,17 @@ sb_status sb_validate(const sb_model *model, const sb_params *params);
 sb_status sb_create(const sb_model *model, const sb_params *params, void *workspace,
                     size_t bytes, void *stream, sb_decoder **out);
 
-/* Largest workspace (bytes) a decoder made by sb_create_noalloc can use, the
- * fp32 projection's split states and row scales and the beams' L_x not
- * counted (the static array has room for them behind it). */
+/* Largest workspace (bytes) a decoder made by sb_create_noalloc can use, not
+ * counting the beams' L_x and what the fp32 projection keeps besides its copy
+ * of W_out (split states, row scales, lists): the static array has another
+ * 36 MiB behind it for these. */
 #define SB_NOALLOC_SCRATCH_BYTES (64u << 20)
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): sb_create
  * without a caller workspace. The decoder uses the library's static scratch,
- * a device array of SB_NOALLOC_SCRATCH_BYTES that each GPU the library runs
- * on holds until the process ends, and static host storage for the decoder
+ * a device array (SB_NOALLOC_SCRATCH_BYTES and 36 MiB) that each GPU the
+ * library runs on holds until the process ends, and static host storage for the decoder
  * object; the call makes no device or pinned-host allocation (no hipMalloc,
  * hipHostMalloc, hipFree, event or stream creation).
  *  - Shapes whose workspace exceeds the scratch (counted as above) return

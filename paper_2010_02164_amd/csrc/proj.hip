@@ -210,7 +210,7 @@ __device__ __forceinline__ void proj_tile(const DevState &st, const GemmOperands
 // Blocks per row tile for a step of R rows: the rule of the fp32 projection
 // (split_tile_blocks) with 0.7 of a block for a tile's start and epilogue,
 // whose weight is larger next to a third of the MFMAs. Measured at d = 1024,
-// |V| = 32000 (us for 1 / 2 / 3 / 4 blocks): 64 rows 16.7 / 18.4 / 18.7 /
+// |V| = 32000 only (us for 1 / 2 / 3 / 4 blocks): 64 rows 16.7 / 18.4 / 18.7 /
 // 18.8, 128 rows 27.0 / 21.5 / 25.6 / 25.1, 193 rows 43.6 / 34.6 / 39.2 /
 // 30.6, 320 rows 54.6 / 42.9 / 43.3 / 47.0, 640 rows 100.5 / 73.7 / 73.0 /
 // 64.7, 5120 rows 842 / 626 / 553 / 495.

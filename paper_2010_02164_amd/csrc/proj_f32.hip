@@ -257,7 +257,7 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
 // load of the fullest compute unit, its tiles times (blocks + 0.35 for a
 // tile's start and epilogue); the odd tile of a compute unit runs there
 // without a second workgroup to hide its latencies and counts 1.35. Measured
-// at d = 1024, |V| = 32000 (us for 1 / 2 / 3 / 4 blocks): 128 rows 43.0 /
+// at d = 1024, |V| = 32000 only (us for 1 / 2 / 3 / 4 blocks): 128 rows 43.0 /
 // 36.0 / 45.7 / 41.1, 193 rows 70.8 / 58.8 / 66.5 / 55.4, 320 rows 94.3 /
 // 76.6 / 81.0 / 88.3, 384 rows 110.8 / 91.8 / 85.5 / 91.3, 640 rows 183.2 /
 // 152.7 / 150.7 / 133.9; the rule takes the fastest in each.
