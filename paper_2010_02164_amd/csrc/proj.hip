@@ -192,11 +192,12 @@ __device__ __forceinline__ void proj_tile(const DevState &st, const GemmOperands
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int reg = 0; reg < 16; ++reg) acc[0][b][reg] += acc[1][b][reg];
-  // The sums are formed here: left to the compiler they move into the epilogue,
-  // block by block, and both halves stay in registers beside its key lists
-  // (16 keys: 256 registers and 18 spilled, now 237 and none).
+  // With 16 keys the sums are formed here: left to the compiler they move into
+  // the epilogue, block by block, and both halves stay in registers beside its
+  // key lists (256 registers and 18 spilled, now 237 and none).
+  if constexpr (KB == 16)
 #pragma unroll
-  for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(acc[0][b]));
+    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(acc[0][b]));
   if constexpr (KV) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)

@@ -214,8 +214,9 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
     some = all || __any(any);
   }
   auto finish = [&](f16v *tot, auto &&wanted) {
+    if constexpr (KB == 16)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
+      for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
     tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R, wanted);
   };
   if (!all) {
