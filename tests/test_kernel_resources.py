@@ -52,13 +52,14 @@ def kernels(native_lib, tmp_path_factory):
 
 
 def test_beam_update_registers(kernels):
-    """Two 8-wave beams per compute unit (128 registers a lane): the
-    recomputation of saturated tiles must not set the beam update's
-    registers, nor be there where full tile lists rule it out."""
+    """Two 8-wave beams per compute unit (128 registers a lane; 168, three waves
+    per SIMD, for the row merge by itself): the recomputation of saturated tiles
+    must not set the kernels' registers, nor be there where full tile lists rule
+    it out."""
     beam = {k: v for k, v in kernels.items() if "k_beam" in k or "k_rowmerge" in k}
     assert len(beam) >= 10
     for name, (vgprs, spills) in beam.items():
-        assert vgprs <= 128 and spills == 0, (name, vgprs, spills)
+        assert vgprs <= (168 if "k_rowmerge" in name else 128) and spills == 0, (name, vgprs, spills)
 
 
 def test_projection_registers(kernels):
