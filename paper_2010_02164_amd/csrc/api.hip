@@ -247,13 +247,9 @@ __global__ void k_set_queued(DevCtrl *c, int32_t nq) {
 // pinned host memory) the tokens, positions and lengths come from there.
 __global__ __launch_bounds__(256) void k_debug_rows(DevState st, const int32_t *in, int32_t R) {
   const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r == 0) {
-    st.ctrl->R = R;
-    st.ctrl->far = 0;
-  }
+  if (r == 0) st.ctrl->R = R;
   if (r >= R) return;
   st.r_hsrc[r] = r;
-  if (st.r_far) st.r_far[r] = 0;
   if (in) {
     st.r_y[r] = in[r];
     st.r_t[r] = in[R + r];

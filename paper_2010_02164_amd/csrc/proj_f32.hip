@@ -314,7 +314,7 @@ __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
   const int R = st.ctrl->R, kinds = st.ctrl->w_kinds | st.ctrl->far;
   if (R <= 0 || kinds < 0) return;   // kinds is 0 or above: tested here so that the loads are one wait
   __shared__ SplitSmem<KB> sm;
-  if (kinds == 0) split_walk<KB, true>(st, sm, R);
+  if (__builtin_expect(kinds == 0, 1)) split_walk<KB, true>(st, sm, R);
   else split_walk<KB, false>(st, sm, R);
 }
 

@@ -136,7 +136,8 @@ __device__ __forceinline__ void rec_tile_f32(const DevState &st, float (*red)[RT
       far += fabsf(hv[q]) < SPLIT_H_MIN ? (hv[q] == 0.0f ? 1 : d) : 0;
     }
     // Rare; one add per row and tile (a row's 16 threads are neighbouring lanes).
-    if (const unsigned long long any = __ballot(far != 0)) {
+    const unsigned long long any = __ballot(far != 0);
+    if (__builtin_expect(any != 0ull, 0)) {
       far += (int)dpp_partner<0>((uint32_t)far);
       far += (int)dpp_partner<1>((uint32_t)far);
       far += (int)dpp_partner<2>((uint32_t)far);

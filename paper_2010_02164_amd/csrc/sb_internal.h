@@ -142,7 +142,8 @@ struct DevState {
   int32_t *w_nfar;         // fp32: [S * 4] far values of a 32-row slice, -1: the slice needs the fp32 MFMA
   FarValue *w_far;         // fp32: [S * 4][SPLIT_FAR]
   unsigned char *hsplit;   // fp32: the step's new states split (split_state_off)
-  int32_t *r_far;          // fp32: [R_max] new states of the row that the pairs do not suit (split_row_fp32)
+  int32_t *r_far;          // fp32: [R_max] new states of the row that the pairs do not suit (split_row_fp32);
+                           // all 0 when the recurrence starts
   // sizes and parameters
   int32_t n, k, d, V, M, max_len_cap, refill_thr, S, R_max, dtype, kv_layers, max_inputs;
   int32_t attn;        // 1: projection input = h + layer-mean attention read-out

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
   DevCtrl *c = st.ctrl;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n = st.n, k = st.k, nslots = n * k;
-  const int nq = c->n_queued, cursor = c->cursor;
+  const int nq = c->n_queued, cursor = c->cursor, far = c->far;
   const int b0 = min(n, tid * PER), nb = min(n, b0 + PER) - b0;
   const bool cap = st.cap != 0;
 
@@ -381,7 +381,6 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     st.r_y[r] = steps == 0 ? 0 : y;                 // and the start symbol
     st.r_t[r] = steps + 1;
     st.r_Lx[r] = x.lx;
-    if (st.r_far) st.r_far[r] = 0;
     if (st.rec_i8) {
       st.haux[r].F = 1;
       st.haux[r].n = 0;
@@ -398,6 +397,8 @@ __global__ __launch_bounds__(SCHED_THREADS) void k_sched(DevState st) {
     for (int s = tid; s < nslots; s += (int)blockDim.x) emit(s, st.s_tok[s]);
   }
 
+  if (far)   // the step before counted some
+    for (int r = tid; r < st.R_max; r += (int)blockDim.x) st.r_far[r] = 0;
   if (tid == 0) {
     c->cursor = cursor + admit;
     c->live = live + admit;
@@ -435,14 +436,15 @@ __global__ void k_init(DevState st, bool create) {
   }
   if (i < st.n * st.k) {
     st.s_status[i] = SLOT_EMPTY;
+    if (st.r_far && i < st.R_max) st.r_far[i] = 0;   // R_max <= n k
   }
   if (i < st.max_inputs) st.o_count[i] = 0;
-  if (i == 0) {
-    DevCtrl z = {};
-    z.done = 1;
-    z.w_kinds = create ? 0 : st.ctrl->w_kinds;   // set by the split of W_out that follows
-    *st.ctrl = z;
-  }
+  // The control block, a word per thread (w_kinds is set by the split of W_out
+  // after the first reset, and kept).
+  constexpr int WORDS = sizeof(DevCtrl) / 4;
+  static_assert(WORDS <= 256, "one workgroup");
+  if (i < WORDS && (create || i != (int)(offsetof(DevCtrl, w_kinds) / 4)))
+    reinterpret_cast<int32_t *>(st.ctrl)[i] = i == (int)(offsetof(DevCtrl, done) / 4) ? 1 : 0;
 }
 
 }  // namespace
