@@ -29,7 +29,7 @@
 // over its tiles if others share them (tanh of an N(0, 1) sum: one row in 7e8 / d).
 //
 // Bound: at d = 1024, |V| = 32000 a step of up to 64 rows by streaming W_out
-// (131 MB at 5.4 TB/s: 24.4 us, was 31.0), larger ones by the fp16 MFMA at
+// (131 MB at 5.4 TB/s: 24.4 us, was 31.0; plain repeated reads: 18.6), larger ones by the fp16 MFMA at
 // the rate large matrix products reach on this card (1.1 PFLOP/s): 193 rows
 // 55.4 us (was 126.9), 640 rows 134 us (was 362), 2560 rows 529 us (was
 // 1353; K loop 1.07 PFLOP/s, 76 us epilogue). Workgroups of 4 waves, two per
