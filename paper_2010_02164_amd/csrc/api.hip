@@ -599,7 +599,10 @@ sb_status sb_create_noalloc(const sb_model *model, const sb_params *params, void
     return SB_E_INVALID_ARG;
   }
   const Layout L = layout_of(*model, *params);
-  const size_t need = L.total - L.extra;
+  // Counted as when every slot kept its row, in place of the beams' masks: the
+  // line between accepted and refused shapes stays where it was.
+  const size_t beams = pool_of(*params), slots = beams * params->k;
+  const size_t need = L.total - L.extra + up(slots * 4) - up(beams * 4);
   if (need > SB_NOALLOC_SCRATCH_BYTES || L.total > SCRATCH_BYTES) {
     char msg[256];
     snprintf(msg, sizeof msg,

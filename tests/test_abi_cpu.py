@@ -123,3 +123,21 @@ def test_status_strings(native_lib):
     for s in range(8):
         assert native_lib.sb_status_string(s)
     assert native_lib.sb_destroy(None) == N.SB_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("k,n,V,max_len,inputs,refused", [
+    (13, 1324, 32, 105, 184, True), (13, 1320, 32, 105, 184, False),
+    (8, 165, 61580, 64, 3, True), (8, 164, 61580, 64, 3, False)])
+def test_noalloc_limit(native_lib, k, n, V, max_len, inputs, refused):
+    """Shapes next to the static scratch's limit, on either side of it (without
+    a GPU an accepted one fails later)."""
+    m = make_model(V, 256, "bf16", 0.5, 1, 1, 1, 0, 0)
+    p = make_params(k, n, 0.25, 2.0, 1, "var_stream", max_len, inputs)
+    h = ctypes.c_void_p()
+    if refused:
+        assert native_lib.sb_create_noalloc(ctypes.byref(m), ctypes.byref(p), None, ctypes.byref(h)) == N.SB_E_WORKSPACE
+    else:
+        import torch
+        if torch.cuda.is_available():
+            pytest.skip("made-up weight pointers: not on a GPU")
+        assert native_lib.sb_create_noalloc(ctypes.byref(m), ctypes.byref(p), None, ctypes.byref(h)) == N.SB_E_HIP
