@@ -204,8 +204,8 @@ __device__ __forceinline__ void proj_tile(const DevState &st, const GemmOperands
     for (int b = 0; b < NB; ++b)
       kv_store_block(st, acc[0][b], vt * TV + 32 * wv, lane >> 5, r0 + 32 * b + (lane & 31), R);
   } else {
-    tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return acc[0][b]; }, vt, wv, r0, R,
-                          [](int) { return true; });
+    tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return acc[0][b]; }, vt, wv, R,
+                          [r0](int s, int l) { return r0 + s + l; });
   }
 }
 

@@ -122,18 +122,18 @@ __device__ __forceinline__ void write_record(const DevState &st, int j, int vt, 
                 __float_as_uint(rec[4 * x + 3])};
 }
 
-// Epilogue of a tile of NB blocks (rows from r0) of vocabulary tile vt, by a
-// workgroup of 4 waves: wave wv's lane lists of its 32-token slice of each
-// block (logits z(b)), then one thread per row merges the four slices, for
-// the rows that are `wanted`. Ends with a barrier: LDS may be reused.
-template <int KB, int NB, class Z, class Wanted>
+// Epilogue of a tile of NB blocks (its row s + l is row(s, l), s the same in every
+// lane; R or above past the last) of vocabulary tile vt, by a workgroup of 4 waves: wave wv's lane lists of its
+// 32-token slice of each block (logits z(b)), then one thread per row merges the
+// four slices. Ends with a barrier: LDS may be reused.
+template <int KB, int NB, class Z, class Row>
 __device__ __forceinline__ void tile_epilogue(const DevState &st, float (*xch)[32 * TILE_BLOCKS][part_width(KB)],
-                                              Z &&z, int vt, int wv, int r0, int R, Wanted &&wanted) {
+                                              Z &&z, int vt, int wv, int R, Row &&row) {
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int v0 = vt * TV;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int j = r0 + 32 * b + l32;
+    const int j = row(32 * b, l32);
     const float bias = (v0 == 0 && j < R) ? st.beta * (float)(st.r_t[j] - st.r_Lx[j]) : 0.0f;
     float m, s;
     TopK<KB> tk;
@@ -146,9 +146,9 @@ __device__ __forceinline__ void tile_epilogue(const DevState &st, float (*xch)[3
     }
   }
   __syncthreads();
-  if (tid < 32 * NB && r0 + tid < R && wanted(r0 + tid)) {
+  if (tid < 32 * NB && row(0, tid) < R) {
     const float *sl[4] = {xch[0][tid], xch[1][tid], xch[2][tid], xch[3][tid]};
-    write_record<KB>(st, r0 + tid, vt, sl);
+    write_record<KB>(st, row(0, tid), vt, sl);
   }
   __syncthreads();
 }

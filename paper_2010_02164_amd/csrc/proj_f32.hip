@@ -25,8 +25,8 @@
 //    smaller one (split_min_terms), takes its products on the fp32 MFMA.
 // The recurrence counts the states of a row that are zero, and those below 2^-29,
 // which the pairs do not hold; a row with one of these, or with fewer than
-// 32 + d / 4 others, takes its products on the fp32 MFMA too, in a second pass
-// over its tiles if others share them (tanh of an N(0, 1) sum: one row in 7e8 / d).
+// 32 + d / 4 others, takes its products on the fp32 MFMA too, after the pairs'
+// pass over its tiles if others share them (tanh of an N(0, 1) sum: one row in 7e8 / d).
 //
 // Bound: at d = 1024, |V| = 32000 a step of up to 64 rows by streaming W_out
 // (131 MB at 5.4 TB/s: 24.4 us, was 31.0; plain repeated reads: 18.6), larger ones by the fp16 MFMA at
@@ -125,8 +125,8 @@ __device__ __forceinline__ void split_mainloop(unsigned char (*stage)[NBM * SPLI
 // k + 16, then the halves added, the sums the recompute of a saturated tile
 // repeats (beam.hip). The states pass through the same LDS buffers, in
 // fragments [4 pieces][64 lanes][4 floats]. Single steps with every tile here,
-// d = 1024, |V| = 32000: 193 / 640 rows 197 / 421 us (110 / 202 on pairs; 250 /
-// 490 with the projection on the fp32 MFMA throughout, in 8-wave workgroups).
+// d = 1024, |V| = 32000: 193 / 640 rows 200 / 411 us (110 / 200 on pairs; 250 /
+// 500 with the projection on the fp32 MFMA throughout, in 8-wave workgroups).
 template <int NB>
 __device__ __forceinline__ void fp32_mainloop(unsigned char (*stage)[NBM * SPLIT_CHUNK], const float *wl,
                                               const float *sl, const uint32_t *row, int d, f16v *tot) {
@@ -151,38 +151,43 @@ __device__ __forceinline__ void fp32_mainloop(unsigned char (*stage)[NBM * SPLIT
   storeS(stage[0]);
   loadS(min(1, nch - 1));
   __syncthreads();
+  auto half = [&](int c0, int c1, f16v *acc) {
 #pragma unroll 1
-  for (int c = 0; c < nch; ++c) {
-    if (c == nch / 2) {
+    for (int c = c0; c < c1; ++c) {
+      if (c + 1 < nch) storeS(stage[(c + 1) & 1]);
+      loadS(min(c + 2, nch - 1));
+      const unsigned char *buf = stage[c & 1] + lane16;
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        first[b] = tot[b];
-        tot[b] = f16v{};
-      }
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const f4 x = *reinterpret_cast<const f4 *>(buf + b * BLOCK + q * FRAG);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][e], x[e], acc[b], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      loadA(min(c + 1, nch - 1));
+      __syncthreads();
     }
-    if (c + 1 < nch) storeS(stage[(c + 1) & 1]);
-    loadS(min(c + 2, nch - 1));
-    const unsigned char *buf = stage[c & 1] + lane16;
+  };
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const f4 x = *reinterpret_cast<const f4 *>(buf + b * BLOCK + q * FRAG);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) tot[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][e], x[e], tot[b], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    loadA(min(c + 1, nch - 1));
-    __syncthreads();
-  }
+  for (int b = 0; b < NB; ++b) first[b] = f16v{};
+  half(0, nch / 2, first);
+  half(nch / 2, nch, tot);
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int r = 0; r < 16; ++r) tot[b][r] = first[b][r] + tot[b][r];
 }
 
-// What k_split_wout found in W_out besides plain rows (bits of DevCtrl::w_kinds).
-constexpr int KIND_FAR = 1, KIND_FP32 = 2;
+template <int KB, int NB, class Row>
+__device__ __forceinline__ void split_finish(const DevState &st, SplitSmem<KB> &sm, f16v *tot, int vt, int wv, int R,
+                                             Row &&row) {
+  if constexpr (KB == 16)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
+  tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, R, row);
+}
 
 // Tile: vocabulary tile vt x NB blocks of 32 rows from row r0.
 template <int KB, bool PLAIN, int NB>
@@ -190,69 +195,66 @@ __device__ __forceinline__ void split_tile(const DevState &st, SplitSmem<KB> &sm
   constexpr int D = NB >= 4 ? 2 : NB == 3 ? 3 : 4;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int slice = vt * 4 + wv;
-  const float *states = static_cast<const float *>(st.proj_in);   // under 4 GiB
-  // The lane, and the offset of its row of block b: formed anew for each use, as
-  // the K loops leave no register to keep them in.
-  auto lane_again = [&] {
-    int l = threadIdx.x & 63;
-    asm volatile("" : "+v"(l));
-    return l;
-  };
-  auto row_at = [&](int b, int l) { return (uint32_t)min(r0 + 32 * b + (l & 31), R - 1) * (uint32_t)st.d; };
-  // Which of the tile's rows need the fp32 MFMA (the same in every wave).
-  bool all = false, some = false;
-  if constexpr (!PLAIN) {
-    bool any = false, every = true;
+  const int slice = vt * 4 + wv, nch = st.d / SPLIT_K;
+  const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
+  f16v tot[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const bool f = split_row_fp32(st, min(r0 + 32 * b + (lane & 31), R - 1));
-      any |= f;
-      every &= f;
-    }
-    all = split_tile_fp32(st, vt) || __all(every);
-    some = all || __any(any);
-  }
-  auto finish = [&](f16v *tot, auto &&wanted) {
-    if constexpr (KB == 16)
+  for (int b = 0; b < NB; ++b) tot[b] = f16v{};
+  split_mainloop<NB, D>(sm.stage, st.wout_t + (size_t)slice * nch * SPLIT_CHUNK + lane * 16,
+                        st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
+  const SplitScale sc(st.w_scale + 32 * slice + 4 * h);
 #pragma unroll
-      for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(tot[b]));   // not one by one in the epilogue, beside its lists
-    tile_epilogue<KB, NB>(st, sm.xch, [&](int b) { return tot[b]; }, vt, wv, r0, R, wanted);
-  };
-  if (!all) {
-    f16v tot[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) tot[b] = f16v{};
-    const int nch = st.d / SPLIT_K;
-    const size_t blkstride = (size_t)nch * SPLIT_CHUNK;
-    split_mainloop<NB, D>(sm.stage, st.wout_t + (size_t)slice * nch * SPLIT_CHUNK + lane * 16,
-                          st.hsplit + (size_t)(r0 >> 5) * blkstride + tid * 16, blkstride, nch, tot);
-    const SplitScale sc(st.w_scale + 32 * slice + 4 * h);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
-    if (const int nfar = PLAIN ? 0 : st.w_nfar[slice]) {
-      uint32_t row[NB];
-      const int l = lane_again();
-#pragma unroll
-      for (int b = 0; b < NB; ++b) row[b] = row_at(b, l);
-      add_far<NB>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, h, states, row, tot);
-    }
-    finish(tot, [](int) { return true; });
-  }
-  if constexpr (!PLAIN) {
-    if (!some) return;
-    f16v tot[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) tot[b] = f16v{};
-    const int l = lane_again(), k0 = 16 * (l >> 5);
-    const float *w = static_cast<const float *>(st.W_out) + (size_t)min(32 * slice + (l & 31), st.V - 1) * st.d + k0;
+  for (int b = 0; b < NB; ++b) tot[b] = sc.apply(tot[b]);
+  if (const int nfar = PLAIN ? 0 : st.w_nfar[slice]) {
     uint32_t row[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) row[b] = row_at(b, l) + k0;
-    fp32_mainloop<NB>(sm.stage, w, states + 4 * wv, row, st.d, tot);
-    finish(tot, [&](int r) { return all || split_row_fp32(st, r); });
+    for (int b = 0; b < NB; ++b) row[b] = (uint32_t)min(r0 + 32 * b + (lane & 31), R - 1) * (uint32_t)st.d;
+    add_far<NB>(st.w_far + (size_t)slice * SPLIT_FAR, nfar, h, static_cast<const float *>(st.proj_in), row, tot);
   }
+  split_finish<KB, NB>(st, sm, tot, vt, wv, R, [r0](int s, int l) { return r0 + s + l; });
 }
+
+// The n rows map[0..n) (n > 32 (NB - 1)) of a row tile on the fp32 MFMA.
+template <int KB, int NB>
+__device__ __forceinline__ void fp32_tile(const DevState &st, SplitSmem<KB> &sm, int vt, const int *map, int n,
+                                          int R) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int k0 = 16 * (lane >> 5);
+  const float *w = static_cast<const float *>(st.W_out) +
+                   (size_t)min((vt * 4 + wv) * 32 + (lane & 31), st.V - 1) * st.d + k0;
+  uint32_t row[NB];   // the states are under 4 GiB
+#pragma unroll
+  for (int b = 0; b < NB; ++b) row[b] = (uint32_t)map[min(32 * b + (lane & 31), n - 1)] * (uint32_t)st.d + k0;
+  f16v tot[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) tot[b] = f16v{};
+  fp32_mainloop<NB>(sm.stage, w, static_cast<const float *>(st.proj_in) + 4 * wv, row, st.d, tot);
+  split_finish<KB, NB>(st, sm, tot, vt, wv, R, [map, n, R](int s, int l) { return s + l < n ? map[s + l] : R; });
+}
+
+// Which of a tile's rows (nrows from r0, at most 128) need the fp32 MFMA: all of
+// them where the vocabulary tile does. Every wave finds the same.
+struct Fp32Rows {
+  unsigned long long m[2];   // rows r0 .. + 63 and r0 + 64 .. + 127
+  __device__ Fp32Rows(const DevState &st, bool far, int vt, int r0, int nrows) {
+    const bool every = split_tile_fp32(st, vt);
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const int i = lane + 64 * w;
+      m[w] = every || far ? __ballot(i < nrows && (every || split_row_fp32(st, r0 + i))) : 0ull;
+    }
+  }
+  __device__ int count() const { return __popcll(m[0]) + __popcll(m[1]); }
+  // The rows in order, to LDS.
+  __device__ void list(int *map, int r0) const {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (w < 2 && ((m[w & 1] >> lane) & 1ull))
+      map[(w ? __popcll(m[0]) : 0) + __popcll(m[w & 1] & ((1ull << lane) - 1ull))] = r0 + 64 * w + lane;
+    __syncthreads();
+  }
+};
 
 // Blocks per row tile for a step of R rows: the count that minimizes the
 // load of the fullest compute unit, its tiles times (blocks + 0.35 for a
@@ -285,8 +287,14 @@ __device__ __forceinline__ int split_tile_blocks(int R, int S, int n_cu) {
 // workgroup which drew a full row tile draws a partial one in the next.
 // A step of plain rows only, of W_out and of states (most are), has a walk of its
 // own: a kind looked up per tile, ahead of its K loop, cost 0.3 us per step.
-template <int KB, bool PLAIN>
-__device__ __forceinline__ void split_walk(const DevState &st, SplitSmem<KB> &sm, int R) {
+// Other steps take two: the pairs over the tiles that have rows for them, then,
+// where a workgroup met others, the fp32 MFMA over those, closed up to blocks of
+// 32 in each tile; their records replace the pairs' (a workgroup's own, in both
+// walks). One walk of both kinds does not fit the registers.
+enum WalkKind { WALK_PLAIN, WALK_PAIRS, WALK_FP32 };
+template <int KB, WalkKind KIND>
+__device__ __forceinline__ bool split_walk(const DevState &st, SplitSmem<KB> &sm, int *map, bool far, int R) {
+  bool others = false;   // rows left to the fp32 MFMA
   const int bt = split_tile_blocks(R, st.S, st.n_cu);
   const int nra = (R + 32 * bt - 1) / (32 * bt);
   const int T = st.S * nra;
@@ -300,22 +308,46 @@ __device__ __forceinline__ void split_walk(const DevState &st, SplitSmem<KB> &sm
     int vt, rt;
     order.at(tile, vt, rt);
     const int r0 = rt * bt * 32;
-    switch (min(bt, (R - r0 + 31) >> 5)) {
-      case 1: split_tile<KB, PLAIN, 1>(st, sm, vt, r0, R); break;
-      case 2: split_tile<KB, PLAIN, 2>(st, sm, vt, r0, R); break;
-      case 3: split_tile<KB, PLAIN, 3>(st, sm, vt, r0, R); break;
-      default: split_tile<KB, PLAIN, 4>(st, sm, vt, r0, R); break;
+    if constexpr (KIND != WALK_FP32) {
+      if constexpr (KIND == WALK_PAIRS) {
+        const int nrows = min(32 * bt, R - r0), n = Fp32Rows(st, far, vt, r0, nrows).count();
+        others |= n > 0;
+        if (n == nrows) continue;
+      }
+      constexpr bool PLAIN = KIND == WALK_PLAIN;
+      switch (min(bt, (R - r0 + 31) >> 5)) {
+        case 1: split_tile<KB, PLAIN, 1>(st, sm, vt, r0, R); break;
+        case 2: split_tile<KB, PLAIN, 2>(st, sm, vt, r0, R); break;
+        case 3: split_tile<KB, PLAIN, 3>(st, sm, vt, r0, R); break;
+        default: split_tile<KB, PLAIN, 4>(st, sm, vt, r0, R); break;
+      }
+    } else {
+      const Fp32Rows rows(st, far, vt, r0, min(32 * bt, R - r0));
+      const int n = rows.count();
+      if (n == 0) continue;
+      rows.list(map, r0);
+      switch ((n + 31) >> 5) {
+        case 1: fp32_tile<KB, 1>(st, sm, vt, map, n, R); break;
+        case 2: fp32_tile<KB, 2>(st, sm, vt, map, n, R); break;
+        case 3: fp32_tile<KB, 3>(st, sm, vt, map, n, R); break;
+        default: fp32_tile<KB, 4>(st, sm, vt, map, n, R); break;
+      }
     }
   }
+  return others;
 }
 
 template <int KB>
 __global__ __launch_bounds__(THREADS, 2) void k_proj_split(DevState st) {
-  const int R = st.ctrl->R, kinds = st.ctrl->w_kinds | st.ctrl->far;
-  if (R <= 0 || kinds < 0) return;   // kinds is 0 or above: tested here so that the loads are one wait
+  const int R = st.ctrl->R, far = st.ctrl->far, w_mixed = st.ctrl->w_mixed;
+  if (R <= 0 || w_mixed < 0) return;   // w_mixed is 0 or 1: tested here so that the loads are one wait
   __shared__ SplitSmem<KB> sm;
-  if (__builtin_expect(kinds == 0, 1)) split_walk<KB, true>(st, sm, R);
-  else split_walk<KB, false>(st, sm, R);
+  __shared__ int map[32 * NBM];
+  if (__builtin_expect((w_mixed | far) == 0, 1)) {
+    split_walk<KB, WALK_PLAIN>(st, sm, map, false, R);
+    return;
+  }
+  if (split_walk<KB, WALK_PAIRS>(st, sm, map, far != 0, R)) split_walk<KB, WALK_FP32>(st, sm, map, far != 0, R);
 }
 
 // W_out, once per decoder (one workgroup per 32 vocabulary rows): the window
@@ -432,7 +464,7 @@ __global__ __launch_bounds__(256) void k_split_wout(DevState st) {
   const bool fp32 = __syncthreads_or(few) || nfar > SPLIT_FAR;
   if (tid == 0) {
     st.w_nfar[blockIdx.x] = fp32 ? -1 : nfar;
-    if (fp32 || nfar > 0) atomicOr(&st.ctrl->w_kinds, fp32 ? KIND_FP32 : KIND_FAR);
+    if (fp32 || nfar > 0) st.ctrl->w_mixed = 1;
   }
   const int v = vb + (lane & 31), vtop = tops[lane & 31];
   const float up = ldexpf(1.0f, 15 + 126 - vtop);

@@ -40,7 +40,7 @@ struct DevCtrl {
   int32_t cursor;     // next input to admit (Alg. 1's c)
   int32_t R;          // rows (active candidates) expanded this step
   int32_t far;        // 1: a row of this step is counted in DevState::r_far
-  int32_t w_kinds;    // fp32: 0, or what W_out holds besides plain rows (proj_f32.hip); kept by a reset
+  int32_t w_mixed;    // fp32, 1: W_out holds rows that fp16 pairs do not suit (proj_f32.hip); kept by a reset
   int32_t t_sel;      // smallest 1-based output position among the selected beams
   int32_t live;       // live beams after admission
   int32_t done;       // 1: nothing queued and no beam live

@@ -439,11 +439,11 @@ __global__ void k_init(DevState st, bool create) {
     if (st.r_far && i < st.R_max) st.r_far[i] = 0;   // R_max <= n k
   }
   if (i < st.max_inputs) st.o_count[i] = 0;
-  // The control block, a word per thread (w_kinds is set by the split of W_out
+  // The control block, a word per thread (w_mixed is set by the split of W_out
   // after the first reset, and kept).
   constexpr int WORDS = sizeof(DevCtrl) / 4;
   static_assert(WORDS <= 256, "one workgroup");
-  if (i < WORDS && (create || i != (int)(offsetof(DevCtrl, w_kinds) / 4)))
+  if (i < WORDS && (create || i != (int)(offsetof(DevCtrl, w_mixed) / 4)))
     reinterpret_cast<int32_t *>(st.ctrl)[i] = i == (int)(offsetof(DevCtrl, done) / 4) ? 1 : 0;
 }
 

@@ -445,8 +445,8 @@ def test_expand_f32_small_states(gpu, name, states, up, units, V, d):
     assert np.abs(got[0] - got[1]).max() <= 2.0**-44
 
 
-@pytest.mark.parametrize("V,k,R", [(1000, 4, 70), (8320, 12, 200)])
-def test_expand_f32_rows_of_both_kinds(gpu, V, k, R):
+@pytest.mark.parametrize("V,k,R,one_in", [(1000, 4, 70, 2), (8320, 12, 200, 2), (8320, 5, 333, 9), (1000, 16, 300, 1.2)])
+def test_expand_f32_rows_of_both_kinds(gpu, V, k, R, one_in):
     """Rows that need the fp32 MFMA change no bit of the rows that share their
     step, whose results are those of a step without them."""
     import torch
@@ -457,7 +457,7 @@ def test_expand_f32_rows_of_both_kinds(gpu, V, k, R):
     E[1::2] *= np.float32(2.0**-33)      # states of odd tokens
     wl = dataclasses.replace(wl, E=E, W_h=Wh)
     rng = np.random.default_rng(95)
-    y = rng.integers(0, V, R).astype(np.int32)
+    y = rng.integers(0, V // 2, R).astype(np.int32) * 2 + (rng.random(R) < 1 / one_in).astype(np.int32)
     y[:40] &= ~1                         # a block of plain rows, then both kinds
     t = rng.integers(1, 40, R).astype(np.int32)
     h = torch.zeros(R, d, device="cuda")
